@@ -1264,7 +1264,12 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_dims, b->host_dims.data(), sizeof(int32_t) * b->host_dims.size(), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return device_fail(e, "upload stats tables");
-    b->stats_tables = cpm::StatsTables{d_label_off, d_dims, n, b->ndim, (int64_t)labels};
+    int64_t max_labels = 0;
+    for (int32_t i = 0; i < n; ++i) max_labels = std::max(max_labels, (int64_t)n_cells[i] + 1);
+    // the reductions' partial sums share the centroid scratch, which holds
+    // nothing between calls
+    b->stats_tables = cpm::StatsTables{d_label_off, d_dims, n, b->ndim, (int64_t)labels, max_labels,
+                                       reinterpret_cast<double *>(ws + bl.scratch_c)};
     b->scratch_v = reinterpret_cast<int32_t *>(ws + bl.scratch_v);
     b->scratch_s = reinterpret_cast<int32_t *>(ws + bl.scratch_s);
     b->scratch_c = reinterpret_cast<int64_t *>(ws + bl.scratch_c);

@@ -203,6 +203,8 @@ struct StatsTables {
     int n;
     int ndim;
     int64_t total_labels;
+    int64_t max_labels;        // labels of the lattice that has most
+    double *part;              // partial sums of the reductions, 3 doubles per label of the batch
 };
 
 // Launchers.  All asynchronous on `stream`.
