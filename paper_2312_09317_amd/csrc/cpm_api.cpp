@@ -1425,19 +1425,13 @@ int cpm_batch_sweep_serial(cpm_batch *b, int32_t n_mcs, void *stream)
         return device_fail(e, "to 16-bit working copy");
     for (int32_t m = 0; m < n_mcs; ++m) {
         e = cpm::launch_serial_mcs(b->d_args, b->n, b->ndim, b->act, b->mirror, (uint32_t)b->mcs, parity, st);
+        if (e == hipSuccess && b->act) e = cpm::launch_act_decay(b->act_field, b->total_sites, st);
         if (e != hipSuccess) return device_fail(e, "serial MCS");
         ++b->mcs;
         ++b->mcs_run;
     }
-    // the other counter buffer and the pending delta lists as the next
-    // parallel activation expects them: exact counters, no deltas to re-add
-    for (int32_t i = 0; i < b->n; ++i) {
-        const SweepArgs &a = b->args[i];
-        e = hipMemcpyAsync(a.counters[parity ^ 1], a.counters[parity], sizeof(int32_t) * 2 * ((size_t)b->n_cells[i] + 1),
-                           hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess) e = cpm::launch_fill_i32(a.dcount[parity ^ 1], 0, (size_t)a.tg.n_tiles, st);
-        if (e != hipSuccess) return device_fail(e, "counters after serial MCS");
-    }
+    e = cpm::launch_after_serial(b->d_args, b->stats_tables.label_off, b->n, b->stats_tables.max_labels, parity, st);
+    if (e != hipSuccess) return device_fail(e, "counters after serial MCS");
     if (b->mirror && (e = cpm::launch_batch_mirror(b->d_args, b->n, b->max_sites, false, st)) != hipSuccess)
         return device_fail(e, "from 16-bit working copy");
     return CPM_OK;
@@ -1484,13 +1478,10 @@ int cpm_batch_use_graph(cpm_batch *b, int32_t enabled)
 int cpm_batch_counters(cpm_batch *b, int32_t *d_volume, int32_t *d_surface, void *stream)
 {
     if (!b || !d_volume || !d_surface) return fail(CPM_EINVAL, "NULL argument");
-    for (int32_t i = 0; i < b->n; ++i) {
-        const hipError_t e = cpm::launch_copy_counters(b->args[i].counters[b->activation & 1], b->n_cells[i] + 1,
-                                                       d_volume + b->label_off[i], d_surface + b->label_off[i],
-                                                       as_stream(stream));
-        if (e != hipSuccess) return device_fail(e, "copy counters");
-    }
-    return CPM_OK;
+    const hipError_t e = cpm::launch_batch_copy_counters(b->d_args, b->stats_tables.label_off, b->n,
+                                                         b->stats_tables.max_labels, (int)(b->activation & 1), d_volume,
+                                                         d_surface, as_stream(stream));
+    return e == hipSuccess ? CPM_OK : device_fail(e, "copy counters");
 }
 
 int cpm_batch_cell_stats(cpm_batch *b, int32_t *d_volume, int32_t *d_surface, int64_t *d_centroid_sum, void *stream)

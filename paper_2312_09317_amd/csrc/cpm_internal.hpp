@@ -232,10 +232,13 @@ hipError_t launch_contacts(const SweepArgs &a, int ndim, int n_types, int64_t *o
 hipError_t launch_batch_cell_stats(const SweepArgs *d_args, const int64_t *d_label_off, int n_lattices, int ndim,
                                    size_t max_sites, int64_t max_bricks, size_t total_labels, int32_t *v_out,
                                    int32_t *s_out, int32_t *ref, int64_t *cent, hipStream_t stream);
-// One MCS of the serial CPM on every lattice of a batch (one wave each);
-// counters: the exact buffer `parity`.
+// One MCS of the serial CPM on every lattice of a batch (one wave each),
+// without the Act decay; counters: the exact buffer `parity`.
 hipError_t launch_serial_mcs(const SweepArgs *d_args, int n_lattices, int ndim, bool act, bool mirror, uint32_t mcs,
                              int parity, hipStream_t st);
+// Every lattice's other counter buffer and pending delta lists after serial MCS.
+hipError_t launch_after_serial(const SweepArgs *d_args, const int64_t *d_label_off, int n_lattices, int64_t max_labels,
+                               int parity, hipStream_t st);
 // Per site, how many lattices of a batch hold a cell there (all lattices of
 // one size, n_sites each, packed back to back).
 hipError_t launch_occupancy(const int32_t *lattices, int n_lattices, size_t n_sites, int32_t *counts,
@@ -295,6 +298,9 @@ hipError_t launch_centroids(const SweepArgs &a, int ndim, int32_t n_cells, int32
 hipError_t launch_copy_dirs(const int4 *pdir, int32_t n_labels, int32_t *out, hipStream_t stream);
 hipError_t launch_copy_counters(const int32_t *pairs, int32_t n_labels, int32_t *v_out,
                                 int32_t *s_out, hipStream_t stream);
+// The counters (buffer `parity`) of every lattice of a batch, packed per label.
+hipError_t launch_batch_copy_counters(const SweepArgs *d_args, const int64_t *d_label_off, int n_lattices,
+                                      int64_t max_labels, int parity, int32_t *v_out, int32_t *s_out, hipStream_t stream);
 hipError_t launch_batch_activation(const BatchLaunch &b, uint32_t alpha, int parity, hipStream_t stream);
 hipError_t launch_set_u32(uint32_t *p, uint32_t value, hipStream_t stream);
 // Adds to *bad the number of sites of an int32 lattice labelled outside

@@ -374,7 +374,7 @@ __global__ void fill_i32_kernel(int32_t *p, int32_t value, size_t n)
 __global__ void act_decay_kernel(uint8_t *act, size_t n)
 {
     const size_t i = ((size_t)blockIdx.x * kBlock + threadIdx.x) * 16;
-    if (i + 16 <= n) {
+    if (i + 16 <= n && (reinterpret_cast<uintptr_t>(act) & 15) == 0) {
         uint4 v = *reinterpret_cast<const uint4 *>(act + i);
         uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -386,7 +386,7 @@ __global__ void act_decay_kernel(uint8_t *act, size_t n)
         }
         *reinterpret_cast<uint4 *>(act + i) = make_uint4(w[0], w[1], w[2], w[3]);
     } else {
-        for (size_t j = i; j < n; ++j)
+        for (size_t j = i; j < i + 16 && j < n; ++j)
             if (act[j] > 0) act[j] = (uint8_t)(act[j] - 1);
     }
 }
@@ -397,6 +397,19 @@ __global__ void copy_counters_kernel(const int32_t *pairs, int32_t n_labels, int
     if (i >= n_labels) return;
     v_out[i] = i == 0 ? 0 : pairs[2 * i];
     s_out[i] = i == 0 ? 0 : pairs[2 * i + 1];
+}
+
+// The same for every lattice of a batch (blockIdx.x), outputs packed per
+// label: one launch (one per lattice cost 1.7 us each, 0.4 ms for 250).
+__global__ void __launch_bounds__(kBlock) batch_copy_counters_kernel(const SweepArgs *args, const int64_t *label_off,
+                                                                     int parity, int32_t *v_out, int32_t *s_out)
+{
+    const int64_t o = label_off[blockIdx.x], n = label_off[blockIdx.x + 1] - o;
+    const int32_t *pairs = args[blockIdx.x].counters[parity];
+    for (int64_t i = (int64_t)blockIdx.y * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.y * kBlock) {
+        v_out[o + i] = i == 0 ? 0 : pairs[2 * i];
+        s_out[o + i] = i == 0 ? 0 : pairs[2 * i + 1];
+    }
 }
 
 // Sites whose label lies outside [-1, n_cells], or is an obstacle (-1) in a
@@ -575,6 +588,15 @@ hipError_t launch_copy_counters(const int32_t *pairs, int32_t n_labels, int32_t 
                                 hipStream_t stream)
 {
     copy_counters_kernel<<<blocks_for((size_t)n_labels), kBlock, 0, stream>>>(pairs, n_labels, v_out, s_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_copy_counters(const SweepArgs *d_args, const int64_t *d_label_off, int n_lattices,
+                                      int64_t max_labels, int parity, int32_t *v_out, int32_t *s_out, hipStream_t stream)
+{
+    const unsigned per = (unsigned)std::min<int64_t>((max_labels + kBlock - 1) / kBlock, 64);
+    batch_copy_counters_kernel<<<dim3((unsigned)n_lattices, per), kBlock, 0, stream>>>(d_args, d_label_off, parity, v_out,
+                                                                                       s_out);
     return hipGetLastError();
 }
 

@@ -284,7 +284,7 @@ __host__ __device__ inline int stat_splits(int64_t labels, int lc, int values)
 {
     const int64_t chunks = (labels - 1 + (1 << lc) - 1) >> lc, room = labels * 3 / values;
     const int64_t s = chunks < room ? chunks : room;
-    return s < 1 ? 1 : (int)s;
+    return s < 1 ? 1 : s > 1024 ? 1024 : (int)s;
 }
 
 // Sum over the 2^lc lanes of this lane's aligned group.
@@ -320,15 +320,19 @@ __device__ __forceinline__ bool persistence_lag(const double *mean, const int *c
 
 template <int D, bool AUTO>
 __global__ void __launch_bounds__(kStatThreads) staged_stats_kernel(const StatsTables t, const double *samples,
-                                                                    int n_samples, double interval, int lc, double *part, double *out)
+                                                                    int n_samples, double interval, int lc, int max_splits, double *part,
+                                                                    double *out)
 {
     extern __shared__ __align__(16) unsigned char lds[];
-    const int i = blockIdx.y, tid = threadIdx.x;
+    // blocks of a lattice next to each other (all lattices' first blocks first
+    // left the large lattices' others to the end: 0.28 against 0.25 ms)
+    const int i = (int)(blockIdx.x / (unsigned)max_splits), split = (int)(blockIdx.x % (unsigned)max_splits);
+    const int tid = threadIdx.x;
     const int64_t labels = t.label_off[i + 1] - t.label_off[i];
     const int K = n_samples, m = K - 1, C = 1 << lc;
     const int values = AUTO ? 2 * m : kSums;
     const int splits = stat_splits(labels, lc, values);
-    if ((int)blockIdx.x >= splits) return;  // uniform over the block
+    if (split >= splits) return;  // uniform over the block
     const double *base = samples + t.label_off[i] * n_samples * kRec;
     double L[D];
     for (int d = 0; d < D; ++d) L[d] = (double)t.dims[3 * i + d];
@@ -346,7 +350,7 @@ __global__ void __launch_bounds__(kStatThreads) staged_stats_kernel(const StatsT
 #pragma unroll
     for (int q = 0; q < kSums; ++q) sums[q] = 0.0;
     const double inv_e = exp(-1.0);
-    for (int64_t c0 = 1 + ((int64_t)blockIdx.x << lc); c0 < labels; c0 += (int64_t)splits << lc) {
+    for (int64_t c0 = 1 + ((int64_t)split << lc); c0 < labels; c0 += (int64_t)splits << lc) {
         __syncthreads();  // the previous chunk's readers are done
         for (int q = tid; q < K * C; q += kStatThreads) {
             const int k = q >> lc, cl = q & (C - 1);
@@ -452,7 +456,7 @@ __global__ void __launch_bounds__(kStatThreads) staged_stats_kernel(const StatsT
     }
     // the workgroup's sums: straight to the output when it is the lattice's
     // only one, else `values` doubles of the lattice's part of the buffer
-    double *mine = part + t.label_off[i] * 3 + (int64_t)blockIdx.x * values;
+    double *mine = part + t.label_off[i] * 3 + (int64_t)split * values;
     __syncthreads();
     if (AUTO) {
         double *to = splits == 1 ? out + (int64_t)i * values : mine;
@@ -535,8 +539,8 @@ hipError_t launch_staged(const StatsTables &t, const double *samples, int n_samp
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    staged_stats_kernel<D, AUTO><<<dim3((unsigned)splits, (unsigned)t.n), kStatThreads, lds, stream>>>(
-        t, samples, n_samples, interval, lc, t.part, out);
+    staged_stats_kernel<D, AUTO><<<(unsigned)t.n * (unsigned)splits, kStatThreads, lds, stream>>>(
+        t, samples, n_samples, interval, lc, splits, t.part, out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     finish_stats_kernel<AUTO><<<t.n, 256, 0, stream>>>(t, m, lc, t.part, out);
