@@ -12,11 +12,13 @@ namespace emu {
 constexpr int kIn = 6;        // inputs per point
 constexpr int kHidden = 256;  // width of the three hidden layers
 constexpr int kOut = 8;       // outputs per point
-constexpr int kInPad = 32;    // K of the first layer, padded to one MFMA k-step
-constexpr int kOutPad = 64;   // N of the last layer, padded to one 64-wide GEMM tile
+constexpr int kTile = 16;     // edge of an MFMA tile (16 x 16 x 32)
+constexpr int kStep = 32;     // its k extent
+constexpr int kInPad = 32;    // K of the first layer, padded to one k-step
+constexpr int kOutPad = 32;   // K of the last layer's backward product, likewise
 constexpr int kRows = 64;     // batch rows are padded to a multiple of this
 constexpr int kLayers = 4;
-constexpr int kSplitK = 1024; // K per workgroup in the weight-gradient GEMMs
+constexpr int kSplitK = 1024; // batch rows per workgroup in the weight-gradient products
 
 // Packed fp32 parameter vector: W1 (256 x 6), b1, W2 (256 x 256), b2,
 // W3 (256 x 256), b3, W4 (8 x 256), b4; W[l] is (out x in), row-major.
@@ -26,65 +28,72 @@ constexpr int64_t kW3 = kB2 + kHidden, kB3 = kW3 + kHidden * kHidden;
 constexpr int64_t kW4 = kB3 + kHidden, kB4 = kW4 + kOut * kHidden;
 constexpr int64_t kParams = kB4 + kOut;  // 135,432
 
-enum Epilogue { kEpiPlain = 0, kEpiBias = 1, kEpiBiasGelu = 2, kEpiGeluGrad = 3 };
+// Operands of the matrix products are kept in the order the matrix cores take
+// them: element (row, k) of an operand of `steps` k-steps lies in the 1 KiB
+// fragment of its 16-row tile and 32-wide k-step, at lane 16 ((k mod 32) / 8)
+// + row mod 16, eight consecutive k per lane, so that a wave loads a fragment
+// with one contiguous 16-byte load per lane.
+__host__ __device__ constexpr size_t frag_at(int row, int k, int steps)
+{
+    return ((size_t)(row / kTile) * steps + k / kStep) * (kTile * kStep) +
+           (size_t)((k % kStep / 8) * kTile + row % kTile) * 8 + k % 8;
+}
 
-// C[M x N] = A[M x K] . B[N x K]^T over k in [z * k_chunk, (z + 1) * k_chunk)
-// for workgroup z; bf16 operands, K-contiguous rows; M, N multiples of 64,
-// K and k_chunk multiples of 32.  Only C entries with m < m_store and
-// n < n_store are stored.
-struct GemmArgs {
-    const uint16_t *A;
-    const uint16_t *B;
-    int32_t lda, ldb;
-    int32_t M, N, K, k_chunk;
-    int32_t m_store, n_store;
-    float *C;             // fp32 result (plain / bias / pre-activation); partial z at C + z * c_split
-    int64_t c_split;
-    int32_t ldc;
-    const float *bias;    // per column n
-    uint16_t *out;        // bf16 activation or gradient, row-major
-    int32_t ldo;
-    uint16_t *out_t;      // its transpose (nullable for activations)
-    int32_t ldot;
-    const float *Z;       // pre-activation read by the GELU-gradient epilogue
-    int32_t ldz;
+// bf16 copies of the weights as operands: w[l] rows = outputs, k = inputs
+// (forward); wt[l] rows = inputs, k = outputs (backward; layers 2..4).
+// Rows beyond the layer's outputs and k beyond its inputs are zero.
+struct Copies {
+    uint16_t *w[kLayers];
+    uint16_t *wt[kLayers];
 };
 
-// One segment of the packed parameter vector for the Adam kernel, with its
-// bf16 copies (rows x cols, row-major with pitch ld16) and transposed copy
-// (cols x rows, pitch ldt16).  Biases have no copies.
-struct AdamSeg {
-    int64_t begin;
-    int32_t rows, cols;
-    uint16_t *w16;
-    int32_t ld16;
-    uint16_t *w16_t;
-    int32_t ldt16;
+// One pass over a batch, forward only (y set) or forward and backward.
+struct RowArgs {
+    const float *x;        // n x 6
+    const float *norm;
+    const float *params;
+    Copies c;
+    int32_t n, n_pad;
+    float *y;              // n x 8, the targets' units (forward)
+    const float *targets;  // n x 8 (training)
+    // operands of the weight gradients (rows = units, k = batch rows): inputs
+    // and activations, and dL/dz of the four layers; and the loss partials
+    uint16_t *in_t[kLayers];
+    uint16_t *dz_t[kLayers];
+    float *loss_part;
 };
 
 struct AdamArgs {
     float *param, *m, *v;
-    const float *grad;
-    int64_t n;
     // 1 - beta is passed separately: 1 - 0.999f in fp32 is 1.3e-5 off 0.001
     float lr, beta1, beta2, one_minus_beta1, one_minus_beta2, eps, c1, c2;  // c1, c2: bias corrections 1 - beta^t
-    AdamSeg seg[2 * kLayers];
+    Copies c;
 };
 
-hipError_t launch_gemm(int epi, const GemmArgs &g, hipStream_t st);
-hipError_t launch_split_reduce(const float *part, int splits, int64_t split_stride, int M, int N, int m_store,
-                               int n_store, float *out, int ldo, hipStream_t st);
-hipError_t launch_rowsum(const uint16_t *g_t, int rows, int n_pad, float *out, hipStream_t st);
-hipError_t launch_input(const float *x, int n, int n_pad, const float *norm, uint16_t *out, uint16_t *out_t,
-                        int ldot, hipStream_t st);
-hipError_t launch_output(const float *y, int n, const float *norm, float *out, hipStream_t st);
-hipError_t launch_loss(const float *y, const float *t, int n, int n_pad, const float *norm, uint16_t *g,
-                       uint16_t *g_t, float *loss_rows, hipStream_t st);
-hipError_t launch_loss_sum(const float *loss_rows, int n, float *out, hipStream_t st);
-hipError_t launch_adam(const AdamArgs &a, hipStream_t st);
-hipError_t launch_cast(const AdamSeg &s, const float *param, hipStream_t st);
+struct GradArgs {
+    const uint16_t *in_t[kLayers];
+    const uint16_t *dz_t[kLayers];
+    int32_t n, n_pad;
+    int32_t splits;          // workgroups along the batch; > 1: partial sums to part
+    float *part;             // splits x kParams
+    float *grad;             // kParams
+    const float *loss_part;
+    int32_t loss_parts;
+    float *loss;
+    float *grad_out, *loss_out;  // the caller's copies (nullable)
+    bool update;             // Adam with the gradient just computed
+    AdamArgs adam;
+};
+
+// Forward pass (train: and backward, up to dL/dz of every layer) of n rows.
+// *loss_parts: loss partials written.
+hipError_t launch_rows(const RowArgs &a, bool train, int *loss_parts, hipStream_t st);
+// Weight and bias gradients, the loss, and (update) the Adam step.
+hipError_t launch_grads(const GradArgs &a, hipStream_t st);
+hipError_t launch_adam(const AdamArgs &a, const float *grad, hipStream_t st);
+// The bf16 copies of all weights from the fp32 parameters.
+hipError_t launch_copies(const Copies &c, const float *params, hipStream_t st);
 hipError_t launch_fit_norm(const float *x, const float *t, int n, int log_mask, float *norm, hipStream_t st);
-hipError_t launch_fill_u16(uint16_t *p, uint16_t v, int64_t n, hipStream_t st);
 hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t st);
 
 }  // namespace emu
