@@ -306,16 +306,19 @@ int cpm_batch_workspace_bytes(const cpm_params *params, int32_t n, const int32_t
 int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, int32_t *d_lattices,
                    const int32_t *d_cell_types, uint8_t *d_act, void *d_workspace, size_t workspace_bytes,
                    void *stream, cpm_batch **out);
-/* Runs n_mcs MCS of every lattice.  By default each MCS is one launch of an
+/* Runs n_mcs MCS of every lattice.  By default, where the library chooses the
+ * tiling and the lattices fit, in one launch whose workgroups keep a lattice
+ * each (or a part of a large one) in LDS; else each MCS is one launch of an
  * executable HIP graph captured at the first call (the activations, the Act
- * decay and the MCS counter update, kernel nodes only); the graph is
- * captured on a private stream and launched on `stream`. */
+ * decay and the MCS counter update, kernel nodes only), captured on a private
+ * stream and launched on `stream`. */
 int cpm_batch_sweep(cpm_batch *b, int32_t n_mcs, void *stream);
 /* enabled = 0: cpm_batch_sweep launches the same kernels one by one instead
  * of the graph (same results).  Pure host. */
 int cpm_batch_use_graph(cpm_batch *b, int32_t enabled);
 /* How cpm_batch_sweep launches its work (same results in every mode; pure
- * host): 0 = one replay of the captured MCS graph per MCS (the default),
+ * host): 0 = the default (see cpm_batch_sweep: lattices kept in LDS, or one
+ * replay of the captured MCS graph per MCS),
  * 1 = the graph's kernels one by one, 2 = one persistent launch per call:
  * as many workgroups as the GPU holds at once (launched cooperatively, so
  * all are resident) loop over the (lattice, tile) work table and meet at a
@@ -324,7 +327,9 @@ int cpm_batch_use_graph(cpm_batch *b, int32_t enabled);
  * whole grid synchronises between activations).  Mode 2 needs batches swept
  * in place (k = 1; CPM_ENOTSUP otherwise).  A barrier wait is bounded (see
  * cpm_batch_set_barrier_spin_limit): a launch whose wait runs out ends
- * early and leaves the batch invalid, which cpm_batch_attempt_stats and
+ * early and leaves the batch invalid (so does, after a fixed limit of about ten
+ * seconds, a default launch whose parts of one lattice wait for each other),
+ * which cpm_batch_attempt_stats and
  * cpm_batch_check_invariants report as CPM_EDEVICE. */
 int cpm_batch_launch_mode(cpm_batch *b, int32_t mode);
 /* Polls of one barrier wait before a persistent launch gives up (default

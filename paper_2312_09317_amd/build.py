@@ -10,10 +10,11 @@ OUT_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(OUT_DIR, "libcpm.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
-SOURCES = ["cpm_sweep.hip", "cpm_sweep_inst.hip", "cpm_serial.hip", "cpm_kernels.hip", "cpm_stats.hip",
+SOURCES = ["cpm_sweep.hip", "cpm_sweep_inst.hip", "cpm_resident.hip", "cpm_serial.hip", "cpm_kernels.hip", "cpm_stats.hip",
            "emu_kernels.hip", "cpm_api.cpp", "emu_api.cpp"]
 # the activation kernels are instantiated in groups, one compilation each
 SWEEP_PARTS = 7
+RESIDENT_PARTS = 5
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     # keep the compiler from emitting packed FP32 instructions
@@ -33,6 +34,8 @@ def units():
         base = os.path.join(OUT_DIR, os.path.basename(src))
         if src.endswith("cpm_sweep_inst.hip"):
             out += [(src, [f"-DCPM_SWEEP_PART={i}"], f"{base}.{i}.o") for i in range(SWEEP_PARTS)]
+        elif src.endswith("cpm_resident.hip"):
+            out += [(src, [f"-DCPM_RESIDENT_PART={i}"], f"{base}.{i}.o") for i in range(RESIDENT_PARTS)]
         else:
             out.append((src, [], base + ".o"))
     return out

@@ -44,6 +44,11 @@ struct cpm_handle {
     uint64_t activation = 0;         // activations run so far (buffer parity)
     uint64_t attempts_run = 0;       // copy attempts run since init
     std::unique_ptr<DeviceModel> host_model;  // source of the async upload
+    // resident sweeps (the lattice in the LDS of one workgroup)
+    bool resident = false;
+    cpm::ResidentPart whole{};
+    size_t resident_lds = 0;
+    int resident_threads = 0;
     int static_device = -1;          // device whose static workspace the handle holds (cpm_init_static), else -1
 };
 
@@ -86,6 +91,16 @@ struct cpm_batch {
     int mode = 0;                    // 0: one graph replay per MCS, 1: kernels one by one, 2: persistent launch
     cpm::GridBarrier *bar = nullptr; // barrier of the persistent launch
     uint32_t spin_limit = 1u << 20;  // polls of a barrier wait before the launch gives up
+    // resident sweeps (mode 0, where every lattice can be cut into few parts)
+    bool resident = false;
+    const cpm::ResidentPart *d_parts = nullptr;
+    std::vector<cpm::ResidentPart> parts;
+    uint32_t *arrivals = nullptr;
+    size_t resident_lds = 0;
+    int resident_threads = 0;
+    bool parts_meet = false;         // some lattice has several parts
+    uint32_t meetings = 0, tickets = 0;
+    bool lists_pending = false;      // a launch per activation left accepted copies to re-add
     hipGraphExec_t mcs_graph = nullptr;  // one MCS: every activation, act decay, MCS counter
     ~cpm_batch()
     {
@@ -307,6 +322,88 @@ bool tile_geometry(const cpm_params *p, bool mirror, int force_layout, cpm::Tile
                 }
             }
     return finish(0);
+}
+
+// Resident sweeps: how a lattice is cut so that a part's box (`cell` bytes a
+// site), the threshold tables and, for an uncut lattice, the counters fit
+// `budget` bytes of LDS: uncut if that fits, else into the fewest parts, of
+// those the ones with the smallest box.  False when more than max_parts are
+// needed.
+constexpr int kResidentMaxAreas = 32 * 512;  // a thread keeps a bit per attempt of an activation
+constexpr uint32_t kResidentSpinLimit = 1u << 24;
+constexpr int kResidentBatchParts = 16;      // most parts of a batch's lattice
+constexpr size_t kResidentBudget = kLdsLimit - cpm::kResidentStaticLds;
+bool resident_split(const cpm_params *p, size_t cell, int32_t n_labels, int32_t n_ti, size_t budget, int max_parts,
+                    cpm::ResidentSplit &sp, size_t &lds, int &areas)
+{
+    const int s = p->sub, R = p->act_enabled ? 2 : 1;
+    const int na0 = p->dims[0] / (2 * s), na1 = p->dims[1] / (2 * s), na2 = p->ndim == 3 ? p->dims[2] / (2 * s) : 1;
+    const size_t tables = sizeof(uint32_t) * ((size_t)n_ti + (p->act_enabled ? 768 + cpm::resident_eh(cell) : 0));
+    // an area's last accepted copy (k > 1)
+    auto heads = [&](int64_t areas) { return p->attempts > 1 ? (size_t)(areas + 8) / 8 * 16 : 0; };
+    // the kernel multiplies in 32 bits: volumes are below 2^21 and surfaces
+    // below 2^25 in a lattice this small
+    for (int t = 0; t < p->n_types; ++t)
+        if (std::abs((int64_t)p->volume_target[t]) > (1 << 28) ||
+            (p->lambda_surface && std::abs((int64_t)p->surface_target[t]) > (1 << 24)))
+            return false;
+    auto up16 = [](size_t v) { return (v + 15) & ~(size_t)15; };
+    const size_t sites = (size_t)p->dims[0] * p->dims[1] * p->dims[2];
+    // 2D: per colour a bit per area and the list of hot areas, with room for
+    // half of them, or, in an uncut lattice, what there is, if it holds an eighth
+    auto bits = [&](int64_t areas) { return p->ndim == 2 ? (size_t)(areas + 63) / 64 * 32 : 0; };
+    auto lists = [&](int64_t cap) { return (size_t)(8 * cap + 15) / 16 * 16; };
+    const int64_t all = (int64_t)na0 * na1 * na2;
+    lds = up16(sites * cell) + 16 * (size_t)n_labels + tables + heads(all) + bits(all);
+    int64_t cap = p->ndim == 2 ? (all + 1) / 2 : 0;
+    if (lds < budget) cap = std::min<int64_t>(cap, (int64_t)(budget - lds - 15) / 8);
+    if (cap >= all / 8 || p->ndim == 3) lds += lists(cap);
+    else lds = budget + 1;
+    if (s > 15) return false;  // the kernel divides draws by s in 16 bits
+    if (lds <= budget && (int64_t)na0 * na1 * na2 <= kResidentMaxAreas) {
+        sp = cpm::ResidentSplit{{na1, na2}, {1, 1}, (int32_t)cap};
+        areas = na0 * na1 * na2;
+        return true;
+    }
+    int best = 0;
+    for (int q2 = 1; q2 <= std::min(na2, max_parts); ++q2)
+        for (int q1 = 1; q1 <= std::min(na1, max_parts / q2); ++q1) {
+            const int T1 = (na1 + q1 - 1) / q1, T2 = (na2 + q2 - 1) / q2;
+            const int n1 = (na1 + T1 - 1) / T1, n2 = (na2 + T2 - 1) / T2;
+            if (n1 * n2 < 2) continue;
+            const size_t b1 = 2 * (size_t)s * T1 + (n1 > 1 ? R : 0);
+            const size_t b2 = p->ndim == 3 ? 2 * (size_t)s * T2 + (n2 > 1 ? R : 0) : 1;
+            const int64_t ar = (int64_t)na0 * T1 * T2;
+            const size_t bytes = up16((size_t)p->dims[0] * b1 * b2 * cell) + tables + heads(ar) + bits(ar) + lists(p->ndim == 2 ? (ar + 1) / 2 : 0);
+            if (bytes > budget || ar > kResidentMaxAreas) continue;
+            if (best && (n1 * n2 > best || (n1 * n2 == best && bytes >= lds))) continue;
+            best = n1 * n2;
+            lds = bytes;
+            areas = (int)ar;
+            sp = cpm::ResidentSplit{{T1, T2}, {n1, n2}, p->ndim == 2 ? (int32_t)((ar + 1) / 2) : 0};
+        }
+    return best > 0;
+}
+
+// Threads of a resident workgroup: two halves of one thread per area, up to all.
+int resident_threads(int areas) { return std::min(cpm::kResidentMaxThreads, std::max((areas + 63) / 64 * 128, 256)); }
+
+// Where the library chooses the tiling.
+bool library_tiling(const cpm_params *p)
+{
+    return p->layout == 0 && !p->tile[0] && !p->tile[1] && !p->tile[2] && !p->tile_order;
+}
+
+// Thread areas up to which one lattice sweeps faster in the LDS of a single
+// workgroup than by a launch per activation, which costs 5.5 to 6 us however
+// small it is (us per 4 MCS, resident : launches): 2D k = 1, 224^2 (3,136
+// areas) 322 : 385, 256^2 451 : 382; 2D k = 4, 144^2 (1,296) 276 : 301,
+// 160^2 310 : 309; 3D k = 1, 40^3 (1,000, the most the LDS holds) 1,254 :
+// 1,457; 3D k = 8 loses from 28^3 on (916 : 799).
+int resident_areas(const cpm_params *p)
+{
+    if (p->ndim == 3) return p->attempts == 1 ? 1280 : 0;
+    return p->attempts == 1 ? 3136 : 1296;
 }
 
 // The layout the parameters ask for (0 in cpm_params = the library's choice).
@@ -817,6 +914,15 @@ int init_impl(const cpm_params *params, int32_t *d_lattice, const int32_t *d_cel
                : use_act_words(params, n_cells) ? cpm::kWordsPackedAct
                : single >= 0 ? cpm::kWords32
                : n_cells <= kMaxPackedCells ? cpm::kWordsPacked : cpm::kWords32;
+    if (library_tiling(params) && (h->words == cpm::kWords16 || h->words == cpm::kWordsPackedAct)) {
+        int areas = 0;
+        cpm::ResidentSplit sp{};
+        h->resident = resident_split(params, h->words == cpm::kWords16 ? 2 : 4, n_cells + 1, h->host_model->n_ti,
+                                     kResidentBudget, 1, sp, h->resident_lds, areas) &&
+                      areas <= resident_areas(params);
+        h->whole = cpm::ResidentPart{0, 1, 0, sp.T[0], 0, sp.T[1], n_cells + 1, sp.hot_cap};
+        h->resident_threads = resident_threads(areas);
+    }
     *out = h.release();
     return CPM_OK;
 }
@@ -825,12 +931,56 @@ int init_impl(const cpm_params *params, int32_t *d_lattice, const int32_t *d_cel
 
 namespace {
 
+// Meetings of a lattice's parts in a resident launch.
+uint32_t resident_meetings(int32_t n_mcs, uint32_t n_act, bool act)
+{
+    return 1u + (uint32_t)n_mcs * n_act + (act ? (uint32_t)n_mcs - 1u : 0u);
+}
+
+// MCS per resident launch: as many as keep a launch to a fraction of a second.
+int32_t resident_chunk(uint32_t n_act) { return (int32_t)std::max<uint32_t>(1u, 65536u / n_act); }
+
+// n_mcs MCS of a single lattice kept in LDS.
+int sweep_resident_impl(cpm_handle *h, int32_t n_mcs, uint32_t n_act, hipStream_t st)
+{
+    const size_t n_sites = (size_t)h->L[0] * h->L[1] * h->L[2];
+    // directions are updated from the lattice after every MCS
+    const int32_t chunk = h->pdir ? 1 : resident_chunk(n_act);
+    cpm::ResidentCall c{};
+    c.one = &h->args;
+    c.whole = h->whole;
+    c.grid = 1;
+    c.threads = h->resident_threads;
+    c.lds = h->resident_lds + cpm::kResidentStaticLds;
+    c.ndim = h->ndim;
+    c.single = h->args.single_type >= 0;
+    c.k1 = h->k == 1;
+    c.ext = h->args.pdir || h->args.chem;
+    for (int32_t done = 0; done < n_mcs;) {
+        const int32_t n = std::min(chunk, n_mcs - done);
+        c.launch = cpm::ResidentLaunch{nullptr, nullptr, nullptr, 0, 0, (uint32_t)h->mcs, n, n_act, 0,
+                                       (int32_t)(h->activation & 1)};
+        const bool d2 = h->ndim == 2;
+        hipError_t e = h->act ? (d2 ? cpm::launch_resident_act32_2d(c, st) : cpm::launch_resident_act32_3d(c, st))
+                              : (d2 ? cpm::launch_resident_u16_2d(c, st) : cpm::launch_resident_u16_3d(c, st));
+        if (e != hipSuccess) return device_fail(e, "resident sweep");
+        h->activation += (uint64_t)n_act * (uint64_t)n;
+        h->mcs += (uint64_t)n;
+        h->attempts_run += (uint64_t)n_sites * (uint64_t)n;
+        done += n;
+        if (h->pdir && (e = persist_step(h, ++h->persist_t, cpm::kWords32, st)) != hipSuccess)
+            return device_fail(e, "persistence update");
+    }
+    return CPM_OK;
+}
+
 // n_mcs MCS of a single lattice.
 int sweep_impl(cpm_handle *h, int32_t n_mcs, hipStream_t st)
 {
     int64_t sd = 1;
     for (int d = 0; d < h->ndim; ++d) sd *= h->s;
     const uint32_t n_act = (uint32_t)(((int64_t)1 << h->ndim) * sd / h->k);
+    if (h->resident) return sweep_resident_impl(h, n_mcs, n_act, st);
     const size_t n_sites = (size_t)h->L[0] * h->L[1] * h->L[2];
     hipError_t e;
     if (h->words == cpm::kWordsPacked &&
@@ -1017,6 +1167,7 @@ struct BatchLayout {
     bool act_words;
     bool act16_ok;             // every lattice fits 16-bit label-activity words
     size_t words16;            // their region: one uint16 per site of the batch
+    size_t parts, arrivals;    // resident sweeps: parts of every lattice, arrivals per lattice
     int layout;
 };
 
@@ -1097,6 +1248,10 @@ BatchLayout batch_layout_of(const cpm_params *p, int32_t n, const int32_t *n_cel
     for (int32_t i = 0; i < n; ++i) total_sites += (size_t)p[i].dims[0] * p[i].dims[1] * p[i].dims[2];
     b.words16 = off;
     off = align_up(off + (b.act16_ok ? sizeof(uint16_t) * total_sites : 0));
+    b.parts = off;
+    off = align_up(off + sizeof(cpm::ResidentPart) * (size_t)n * kResidentBatchParts);
+    b.arrivals = off;
+    off = align_up(off + sizeof(uint32_t) * cpm::kResidentArrivalStride * (size_t)n);
     for (const Layout &l : b.lat) {
         b.base.push_back(off);
         off = align_up(off + l.total);
@@ -1211,7 +1366,7 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
     b->d_work = reinterpret_cast<int2 *>(ws + bl.work);
     b->d_mcs = reinterpret_cast<uint32_t *>(ws + bl.mcs);
     b->bar = reinterpret_cast<cpm::GridBarrier *>(ws + bl.barrier);
-    if ((e = cpm::launch_fill_i32(reinterpret_cast<int32_t *>(b->bar), 0, 4, st)) != hipSuccess)
+    if ((e = cpm::launch_fill_i32(reinterpret_cast<int32_t *>(b->bar), 0, sizeof(cpm::GridBarrier) / 4, st)) != hipSuccess)
         return device_fail(e, "clear barrier");
     // one cell type throughout, small lattices and every activity within 5
     // bits: 16-bit label-activity words
@@ -1290,6 +1445,66 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
     L.ext = false;
     for (const SweepArgs &a : b->args) L.ext = L.ext || a.chem != nullptr;
     L.layout = b->layout;
+    // resident sweeps: where the library chooses the tiling and every
+    // lattice can be cut into few parts.  A few large lattices, though, leave
+    // most of the GPU idle that way, and sweep faster by a launch per
+    // activation over all of it (us for one sample and 4 MCS, resident :
+    // launches): 8 of 256^2 644 : 604, 32 of 256^2 644 : 758; 8 of 64..512 per
+    // side 696 : 647, 16 713 : 714, 32 762 : 822, 512 of 160..512 5,134 : 6,561.
+    b->resident = (b->act16 || b->act_words || b->mirror) && !(b->ndim == 3 && b->k > 1);
+    for (int32_t i = 0; i < n && b->resident; ++i) b->resident = library_tiling(&params[i]);
+    if (b->resident) {
+        const size_t cell = b->act16 || b->mirror ? 2 : 4;
+        struct Cut { cpm::ResidentSplit sp; int32_t i; int areas; };
+        std::vector<Cut> cuts;
+        int max_areas = 1;
+        for (int32_t i = 0; i < n && b->resident; ++i) {
+            Cut c{};
+            size_t bytes = 0;
+            c.i = i;
+            b->resident = resident_split(&params[i], cell, n_cells[i] + 1, b->models[i]->n_ti,
+                                         kResidentBudget, kResidentBatchParts, c.sp, bytes, c.areas);
+            b->resident_lds = std::max(b->resident_lds, bytes);
+            max_areas = std::max(max_areas, c.areas);
+            cuts.push_back(c);
+        }
+        b->resident_threads = resident_threads(max_areas);
+        bool cut = false;
+        for (const Cut &c : cuts) cut = cut || c.sp.parts[0] * c.sp.parts[1] > 1;
+        if (max_areas > 2000 && sites < (cut ? (size_t)1500000 : (size_t)750000)) b->resident = false;
+        // the parts that take longest first
+        std::stable_sort(cuts.begin(), cuts.end(), [](const Cut &x, const Cut &y) {
+            const bool mx = x.sp.parts[0] * x.sp.parts[1] > 1, my = y.sp.parts[0] * y.sp.parts[1] > 1;
+            return mx != my ? mx : x.areas > y.areas;
+        });
+        if (b->resident) {
+            for (const Cut &c : cuts) {
+                const SweepArgs &a = b->args[c.i];
+                const int q = c.sp.parts[0] * c.sp.parts[1];
+                b->parts_meet = b->parts_meet || q > 1;
+                for (int j = 0; j < q; ++j) {
+                    cpm::ResidentPart pt{};
+                    pt.lattice = c.i;
+                    pt.n_parts = q;
+                    pt.a1 = j % c.sp.parts[0] * c.sp.T[0];
+                    pt.n1 = std::min(c.sp.T[0], a.na[1] - pt.a1);
+                    pt.a2 = j / c.sp.parts[0] * c.sp.T[1];
+                    pt.n2 = std::min(c.sp.T[1], a.na[2] - pt.a2);
+                    pt.n_labels = n_cells[c.i] + 1;
+                    pt.hot_cap = c.sp.hot_cap;
+                    b->parts.push_back(pt);
+                }
+            }
+            b->d_parts = reinterpret_cast<const cpm::ResidentPart *>(ws + bl.parts);
+            b->arrivals = reinterpret_cast<uint32_t *>(ws + bl.arrivals);
+            e = hipMemcpyAsync(ws + bl.parts, b->parts.data(), sizeof(cpm::ResidentPart) * b->parts.size(),
+                               hipMemcpyHostToDevice, st);
+            if (e == hipSuccess)
+                e = cpm::launch_fill_i32(reinterpret_cast<int32_t *>(b->arrivals), 0,
+                                         (size_t)cpm::kResidentArrivalStride * (size_t)n, st);
+            if (e != hipSuccess) return device_fail(e, "upload parts");
+        }
+    }
     *out = b.release();
     return CPM_OK;
 }
@@ -1323,7 +1538,7 @@ int check_barrier(cpm_batch *b, hipStream_t st)
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return device_fail(e, "read barrier");
     if (g.abort)
-        return fail(CPM_EDEVICE, "a persistent launch of this batch gave up at a grid barrier (spin limit reached); "
+        return fail(CPM_EDEVICE, "a launch of this batch gave up at a barrier between workgroups (spin limit reached); "
                                  "the batch state is invalid");
     if (g.act_overflow)
         return fail(CPM_EDEVICE, "an activity above 31 was written into a batch that sweeps on 16-bit words; "
@@ -1355,6 +1570,53 @@ hipError_t capture_mcs(cpm_batch *b, uint32_t n_act)
 
 }  // namespace
 
+}  // extern "C"
+
+namespace {
+
+// n_mcs MCS of a batch whose lattices stay in LDS.
+int batch_sweep_resident(cpm_batch *b, int32_t n_mcs, uint32_t n_act, hipStream_t st)
+{
+    hipError_t e;
+    if (b->lists_pending &&
+        (e = cpm::launch_after_serial(b->d_args, b->stats_tables.label_off, b->n, b->stats_tables.max_labels,
+                                      (int)(b->activation & 1), st)) != hipSuccess)
+        return device_fail(e, "counters before a resident sweep");
+    b->lists_pending = false;
+    cpm::ResidentCall c{};
+    c.args = b->d_args;
+    c.parts = b->d_parts;
+    c.grid = (int)b->parts.size();
+    c.threads = b->resident_threads;
+    c.lds = b->resident_lds + cpm::kResidentStaticLds;
+    c.ndim = b->ndim;
+    c.single = b->single;
+    c.k1 = b->k == 1;
+    c.ext = b->launch.ext;
+    for (int32_t done = 0; done < n_mcs;) {
+        const int32_t n = std::min(resident_chunk(n_act), n_mcs - done);
+        c.launch = cpm::ResidentLaunch{b->bar, b->arrivals, b->parts_meet ? &b->bar->ticket : nullptr, b->tickets,
+                                       b->meetings, (uint32_t)b->mcs, n, n_act, kResidentSpinLimit,
+                                       (int32_t)(b->activation & 1)};
+        const bool d2 = b->ndim == 2;
+        e = b->act16       ? cpm::launch_resident_act16(c, st)
+            : b->act_words ? (d2 ? cpm::launch_resident_act32_2d(c, st) : cpm::launch_resident_act32_3d(c, st))
+                           : (d2 ? cpm::launch_resident_u16_2d(c, st) : cpm::launch_resident_u16_3d(c, st));
+        if (e != hipSuccess) return device_fail(e, "resident sweep");
+        if (b->parts_meet) b->tickets += (uint32_t)c.grid;
+        b->meetings += resident_meetings(n, n_act, b->act);
+        b->activation += (uint64_t)n_act * (uint64_t)n;
+        b->mcs += (uint64_t)n;
+        b->mcs_run += (uint64_t)n;
+        done += n;
+    }
+    return CPM_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 int cpm_batch_sweep(cpm_batch *b, int32_t n_mcs, void *stream)
 {
     if (!b) return fail(CPM_EINVAL, "batch is NULL");
@@ -1365,6 +1627,8 @@ int cpm_batch_sweep(cpm_batch *b, int32_t n_mcs, void *stream)
     for (int d = 0; d < b->ndim; ++d) sd *= b->s;
     const uint32_t n_act = (uint32_t)(((int64_t)1 << b->ndim) * sd / b->k);
     hipError_t e;
+    if (b->resident && b->mode == 0) return batch_sweep_resident(b, n_mcs, n_act, st);
+    b->lists_pending = true;
     if (b->mode == 0 && !b->mcs_graph && (e = capture_mcs(b, n_act)) != hipSuccess)
         return device_fail(e, "capture MCS graph");
     if (b->mirror && (e = cpm::launch_batch_mirror(b->d_args, b->n, b->max_sites, true, st)) != hipSuccess)
@@ -1432,6 +1696,7 @@ int cpm_batch_sweep_serial(cpm_batch *b, int32_t n_mcs, void *stream)
     }
     e = cpm::launch_after_serial(b->d_args, b->stats_tables.label_off, b->n, b->stats_tables.max_labels, parity, st);
     if (e != hipSuccess) return device_fail(e, "counters after serial MCS");
+    b->lists_pending = false;
     if (b->mirror && (e = cpm::launch_batch_mirror(b->d_args, b->n, b->max_sites, false, st)) != hipSuccess)
         return device_fail(e, "from 16-bit working copy");
     return CPM_OK;

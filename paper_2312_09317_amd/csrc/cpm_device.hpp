@@ -7,11 +7,15 @@
 namespace cpm {
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
-// 32x32->64-bit products, key bumped by the Weyl constants between rounds.
+// 32x32->64-bit products, key bumped by the Weyl constants between rounds;
+// the last ROUNDS of them.
+template <int ROUNDS = 10>
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1)
 {
+    k0 += (uint32_t)(10 - ROUNDS) * 0x9E3779B9u;
+    k1 += (uint32_t)(10 - ROUNDS) * 0xBB67AE85u;
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
+    for (int r = 0; r < ROUNDS; ++r) {
         // each product as one 32x32->64 multiply (both halves at once)
         const uint64_t p0 = (uint64_t)0xD2511F53u * c.x, p1 = (uint64_t)0xCD9E8D57u * c.z;
         const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
@@ -24,6 +28,13 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
 }
 
 __device__ __forceinline__ int wrap_once(int v, int L) { return v < 0 ? v + L : (v >= L ? v - L : v); }
+
+// The same for v in [-L, 2L), L < 2^30, without compares.
+__device__ __forceinline__ int wrap_min(int v, int L)
+{
+    const uint32_t w = min((uint32_t)v, (uint32_t)(v + L));
+    return (int)min(w, w - (uint32_t)L);
+}
 
 // Labels as stored.  int32: the label itself.  The 16-bit working copy holds
 // label + 1 (obstacle -1 -> 0, medium 0 -> 1, cells 1..65534 -> 2..65535),

@@ -178,6 +178,7 @@ struct GridBarrier {
     uint32_t gen;
     uint32_t abort;
     uint32_t act_overflow;  // sticky: an activity too large for 16-bit words was met
+    uint32_t ticket;        // parts taken by resident launches since init (only grows)
 };
 
 // One persistent launch: n_mcs MCS of a batch (every activation, then the
@@ -195,6 +196,56 @@ struct PersistentLaunch {
     void *decay_ptr;
     size_t n_sites;          // sites of the whole batch
 };
+
+// Resident sweeps (cpm_resident.hip): lattices, or parts of them, kept in LDS.
+constexpr int kResidentMaxThreads = 1024;
+constexpr int kResidentQueue = 1024;         // attempts queued for evaluation per workgroup
+constexpr int kResidentList = 192;           // accepted copies listed in LDS per activation
+constexpr int kResidentArrivalStride = 32;   // one cache line of arrivals per lattice
+// LDS of a resident workgroup beside what its lattice sizes (resident_split)
+constexpr int kResidentStaticLds = 8 * kResidentQueue + 30 * kResidentList + 4 * kMaxTypes * kMaxTypes + 8 * 256 + 1136;
+// Entries of the Act exponential's first table (exp(n / 256)) that the
+// activities of 16-bit words (up to 31) and of 32-bit words (255) can reach.
+constexpr int resident_eh(size_t cell) { return cell == 2 ? 880 : 1420; }
+// One workgroup's share of a lattice: areas [a1, a1 + n1) along y and
+// [a2, a2 + n2) along z, whole rows along x.
+struct ResidentPart {
+    int32_t lattice, n_parts, a1, n1, a2, n2, n_labels;
+    int32_t hot_cap;  // room of each colour's list of hot areas (2D)
+};
+// How a lattice is cut: T areas each along y and z (the last ones fewer).
+struct ResidentSplit {
+    int32_t T[2], parts[2];
+    int32_t hot_cap;
+};
+struct ResidentLaunch {
+    GridBarrier *bar;      // abort and act_overflow
+    uint32_t *arrivals;    // kResidentArrivalStride words per lattice; the first counts arrivals since init
+    uint32_t *ticket;      // NULL: part blockIdx.x
+    uint32_t ticket0;      // the ticket of this launch's first part
+    uint32_t meetings;     // meetings of the parts before this launch
+    uint32_t mcs0;
+    int32_t n_mcs;
+    uint32_t n_act;        // activations per MCS
+    uint32_t spin_limit;   // polls of one wait before giving up
+    int32_t parity;        // counter buffer the first activation reads
+};
+struct ResidentCall {
+    const SweepArgs *args;     // batches: device array; NULL for a single lattice
+    const ResidentPart *parts; // batches: device array, one per workgroup
+    const SweepArgs *one;      // a single lattice's arguments (host)
+    ResidentPart whole;        // ... and its one part
+    ResidentLaunch launch;
+    int grid, threads;
+    size_t lds;                // dynamic LDS
+    int ndim;
+    bool single, k1, ext;
+};
+hipError_t launch_resident_u16_2d(const ResidentCall &c, hipStream_t st);
+hipError_t launch_resident_u16_3d(const ResidentCall &c, hipStream_t st);
+hipError_t launch_resident_act32_2d(const ResidentCall &c, hipStream_t st);
+hipError_t launch_resident_act32_3d(const ResidentCall &c, hipStream_t st);
+hipError_t launch_resident_act16(const ResidentCall &c, hipStream_t st);
 
 // Per-lattice tables for the summary statistics of a batch (device arrays).
 struct StatsTables {

@@ -57,8 +57,9 @@ constexpr int kQueue = 128;  // queued attempts per workgroup; the rest are eval
 // Where the sites an attempt reads live.  kBox: an LDS box, coordinates
 // box-local; kFullRow: LDS rows spanning the lattice along x, x global and
 // wrapping, y, z box-local; kDirect: the lattice itself in global memory,
-// every coordinate global and wrapping.
-enum Layout { kBox = 0, kFullRow = 1, kDirect = 2 };
+// every coordinate global and wrapping; kResident: an LDS box whose every
+// coordinate wraps at the box's extent (cpm_resident.hip).
+enum Layout { kBox = 0, kFullRow = 1, kDirect = 2, kResident = 3 };
 
 // A pointer of the sweep arguments as a plain (generic) pointer; loads
 // through a global-memory one converted here stay global loads.
@@ -78,9 +79,14 @@ struct LdsMap {
     int pitch;  // sites per row
     int rows;   // rows per z plane
     int L0, L1, L2;
-    __device__ __forceinline__ int x(int v) const { return LAYOUT == kBox ? v : wrap_once(v, L0); }
+    __device__ __forceinline__ int x(int v) const
+    {
+        return LAYOUT == kBox ? v : LAYOUT == kResident ? wrap_min(v, L0) : wrap_once(v, L0);
+    }
     __device__ __forceinline__ int row(int vy, int vz) const
     {
+        if (LAYOUT == kResident)  // a box in LDS: every product is below 2^24, where 24-bit multiplies run at full rate
+            return (int)__umul24((uint32_t)L0, (uint32_t)wrap_min(vy, L1) + __umul24((uint32_t)L1, (uint32_t)wrap_min(vz, L2)));
         return LAYOUT == kDirect ? L0 * (wrap_once(vy, L1) + L1 * wrap_once(vz, L2)) : pitch * (vy + rows * vz);
     }
     __device__ __forceinline__ int at(int vx, int vy, int vz) const { return x(vx) + row(vy, vz); }

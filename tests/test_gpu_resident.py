@@ -1,0 +1,154 @@
+"""Sweeps of lattices kept in LDS (the library's own choice of tiling) against
+the same sweeps by one launch per activation (an explicit layout), bit for
+bit, where the resident kernel can go wrong: rows that are not whole vectors,
+s from 1 up, several attempts per activation, lists and queues that overflow,
+lattices cut into parts (with every term that reads across a cut), and calls
+of both kinds in turn."""
+import numpy as np
+import pytest
+
+from paper_2312_09317_amd import cpm, inputs
+
+pytestmark = pytest.mark.gpu
+
+J3 = np.array([[0, 3, 5, 1.5], [3, 7, 1.25, -2], [5, 1.25, 9, 0.5], [1.5, -2, 0.5, 0]])
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available()
+    cpm.load()
+    return torch
+
+
+def _params(dims, types=1, T=8.0, **kw):
+    """One cell type, or two and obstacles."""
+    if types == 1:
+        base = dict(J=np.array([[0.0, 6.0], [6.0, 9.0]]), lambda_volume=[0, 2.0], volume_target=[0, 40],
+                    lambda_surface=[0, 0.25], surface_target=[0, 90])
+    else:
+        base = dict(J=J3, lambda_volume=[0, 2.5, 1.0, 0], volume_target=[0, 30, 40, 0], lambda_surface=[0, 0.5, 0.25, 0],
+                    surface_target=[0, 90, 120, 0], obstacle_type=3)
+    base.update(kw)
+    return cpm.Params(ndim=len(dims), dims=dims, temperature=T, seed=11, **base)
+
+
+def _lattice(kind, dims, n, seed, obstacles):
+    shape = tuple(dims) + (1,) * (3 - len(dims))
+    p = 0.03 if obstacles else 0.0
+    if kind == "noise":
+        return inputs.random_labels(shape, n, seed, p_obstacle=p), n
+    return inputs.random_blobs(shape, n, seed=seed, fill=0.4, p_obstacle=p), n
+
+
+def _same(torch, p, lattice, types, explicit, n_mcs):
+    """The library's choice against `explicit`, in two calls."""
+    out = []
+    for q in (p, p.replace(layout=explicit)):
+        sim = cpm.Simulation(q, lattice, types)
+        sim.sweep(1)
+        sim.sweep(n_mcs - 1)
+        torch.cuda.synchronize()
+        assert sim.check_invariants()
+        out.append([sim.lattice.cpu().numpy(), sim.act.cpu().numpy() if sim.act is not None else np.zeros(1)] +
+                   [c.cpu().numpy()[1:] for c in sim.counters()] + [np.array([int(x) for x in sim.attempt_stats()])])
+        sim.close()
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+
+
+SINGLE = [
+    # dims, lattice, cells, types, s, k, T, act
+    ((24, 24), "blobs", 5, 1, 2, 1, 8.0, False),
+    ((30, 42), "blobs", 9, 2, 3, 1, 8.0, False),      # rows of 30 words: no whole vectors
+    ((34, 18), "noise", 300, 1, 1, 1, 30.0, False),   # s = 1, rows of 34
+    ((200, 200), "noise", 3000, 1, 2, 1, 40.0, False),  # every attempt nontrivial: queue and lists overflow
+    ((96, 64), "noise", 500, 2, 4, 8, 40.0, False),   # several attempts per area, many accepted
+    ((64, 64), "blobs", 40, 1, 2, 4, 8.0, True),
+    ((44, 40), "blobs", 20, 2, 2, 1, 8.0, True),
+    ((208, 16), "blobs", 12, 1, 2, 2, 8.0, False),
+    ((180, 180), "noise", 2000, 1, 2, 1, 30.0, True),  # 32-bit words
+    ((16, 24, 20), "blobs", 12, 2, 2, 1, 8.0, False),
+    ((40, 40, 40), "noise", 600, 1, 2, 1, 30.0, False),
+    ((16, 16, 24), "blobs", 9, 2, 2, 1, 8.0, True),
+    ((12, 6, 18), "blobs", 5, 1, 3, 1, 8.0, False),
+]
+
+
+@pytest.mark.parametrize("case", range(len(SINGLE)))
+def test_single_lattice(torch_cuda, case):
+    dims, kind, n, types, s, k, T, act = SINGLE[case]
+    print(f"resident case {SINGLE[case]}", flush=True)
+    lat, n = _lattice(kind, dims, n, 20 + case, types == 2)
+    kw = dict(sub=s, attempts=k)
+    if act:
+        kw.update(lambda_act=[0, 60.0] + ([0.0, 0.0] if types == 2 else []), max_act=[0, 20] + ([0, 0] if types == 2 else []))
+    ct = np.array([0] + [1 + (i % types) for i in range(n)], dtype=np.int32)
+    _same(torch_cuda, _params(dims, types, T, **kw), lat, ct, "in_place" if k == 1 else "box", 5)
+
+
+@pytest.mark.parametrize("incremental", [False, True])
+def test_persistence(torch_cuda, incremental):
+    dims = (24, 20, 28)
+    lat, n = _lattice("blobs", dims, 10, 3, False)
+    p = _params(dims, lambda_persistence=[0, 40.0], persistence_mu=[0, 0.9], persistence_dt=2,
+                persistence_centroids="incremental" if incremental else "recount")
+    print(f"resident persistence incremental={incremental}", flush=True)
+    _same(torch_cuda, p, lat, np.array([0] + [1] * n, dtype=np.int32), "in_place", 6)
+
+
+def _batches_same(torch, params, lats, types, explicit, n_mcs, mode_between=None):
+    out = []
+    for lay in ("auto", explicit):
+        b = cpm.Batch([q.replace(layout=lay) for q in params], lats, types)
+        b.sweep(2)
+        if mode_between and lay == "auto":
+            b.launch_mode(mode_between)  # a launch per activation, then resident again
+            b.sweep(1)
+            b.launch_mode("graph")
+        else:
+            b.sweep(1)
+        b.sweep(n_mcs - 3)
+        torch.cuda.synchronize()
+        assert all(b.check_invariants())
+        out.append([b.lattices.cpu().numpy(), b.act.cpu().numpy() if b.act is not None else np.zeros(1)] +
+                   [c.cpu().numpy() for c in b.counters()] + [np.asarray(b.attempt_stats()).astype(np.int64)])
+    labels = np.cumsum([0] + [len(t) for t in types])[:-1]
+    for v in out:
+        for c in v[2:4]:
+            c[labels] = 0
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+
+
+BATCH = [
+    # lattices (dims), kind, cells, types, s, k, act, chemotaxis
+    ([(640, 512), (288, 300), (64, 48)] * 2, "blobs", 700, 1, 2, 1, True, False),   # cut into parts, and not; 16-bit words
+    ([(640, 600), (512, 528)] * 2, "noise", 900, 1, 2, 1, False, False),
+    ([(640, 600), (480, 528)] * 3, "noise", 900, 2, 2, 1, True, False),             # 32-bit words
+    ([(576, 576)] * 5, "blobs", 500, 1, 4, 8, False, True),
+    ([(1024, 800), (900, 1000)], "noise", 400, 1, 1, 1, False, True),
+    ([(64, 72, 80)] * 6, "blobs", 300, 2, 2, 1, False, False),                      # cut across y and z
+    ([(64, 64, 68), (64, 60, 64)] * 4, "blobs", 300, 2, 2, 1, True, False),
+]
+
+
+@pytest.mark.parametrize("case", range(len(BATCH)))
+def test_batch_with_cut_lattices(torch_cuda, case):
+    dims, kind, n, types, s, k, act, chem = BATCH[case]
+    print(f"resident batch case {BATCH[case]}", flush=True)
+    params, lats, cts = [], [], []
+    for i, d in enumerate(dims):
+        lat, m = _lattice(kind, d, n, 50 + i, types == 2)
+        kw = dict(sub=s, attempts=k, lattice_id=i)
+        if act:
+            kw.update(lambda_act=[0, 60.0] + ([0.0, 0.0] if types == 2 else []), max_act=[0, 20] + ([0, 0] if types == 2 else []))
+        if chem:
+            rng = np.random.default_rng(i)
+            kw.update(lambda_chemotaxis=[0, 9.0], chemotaxis_field=torch_cuda.as_tensor(
+                rng.integers(-16000, 16000, int(np.prod(d)) * len(d)).astype(np.int16)).cuda())
+        params.append(_params(d, types, 8.0 + i, **kw))
+        lats.append(lat)
+        cts.append(np.array([0] + [1 + (j % types) for j in range(m)], dtype=np.int32))
+    _batches_same(torch_cuda, params, lats, cts, "in_place" if k == 1 else "box", 5, mode_between="eager" if case % 2 == 0 else None)
