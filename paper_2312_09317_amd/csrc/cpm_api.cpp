@@ -1055,12 +1055,13 @@ int cpm_cell_stats(cpm_handle *h, int32_t *d_volume, int32_t *d_surface, int64_t
     hipStream_t st = as_stream(stream);
     const size_t n = (size_t)h->n_cells + 1;
     hipError_t e;
-    if ((e = cpm::launch_fill_i32(d_volume, 0, n, st)) != hipSuccess) return device_fail(e, "clear volume");
-    if ((e = cpm::launch_fill_i32(d_surface, 0, n, st)) != hipSuccess) return device_fail(e, "clear surface");
-    if ((e = cpm::launch_count(h->args, h->ndim, d_volume, d_surface, 1, st)) != hipSuccess)
+    int32_t *ref = d_centroid_sum ? h->ref : nullptr;
+    if ((e = cpm::launch_clear_stats(d_volume, d_surface, ref, n, d_centroid_sum, h->ndim, st)) != hipSuccess)
+        return device_fail(e, "clear sums");
+    if ((e = cpm::launch_count(h->args, h->ndim, d_volume, d_surface, 1, st, ref)) != hipSuccess)
         return device_fail(e, "count");
     if (d_centroid_sum) {
-        if ((e = cpm::launch_centroids(h->args, h->ndim, h->n_cells, h->ref, d_centroid_sum, st)) != hipSuccess)
+        if ((e = cpm::launch_centroids(h->args, h->ndim, h->n_cells, ref, d_centroid_sum, st, cpm::kWords32, true)) != hipSuccess)
             return device_fail(e, "centroids");
     }
     return CPM_OK;
@@ -1753,7 +1754,7 @@ int cpm_batch_cell_stats(cpm_batch *b, int32_t *d_volume, int32_t *d_surface, in
 {
     if (!b || !d_volume || !d_surface) return fail(CPM_EINVAL, "NULL argument");
     const hipError_t e = cpm::launch_batch_cell_stats(b->d_args, b->stats_tables.label_off, b->n, b->ndim,
-                                                      b->max_sites, b->max_bricks, (size_t)b->stats_tables.total_labels, d_volume,
+                                                      b->max_bricks, (size_t)b->stats_tables.total_labels, d_volume,
                                                       d_surface, b->scratch_ref, d_centroid_sum, as_stream(stream));
     return e == hipSuccess ? CPM_OK : device_fail(e, "cell stats");
 }

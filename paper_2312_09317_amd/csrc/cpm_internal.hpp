@@ -281,8 +281,8 @@ hipError_t launch_contacts(const SweepArgs &a, int ndim, int n_types, int64_t *o
 // batch, packed per label; ref is scratch of total_labels entries.
 // max_bricks: the largest reduce_brick_count of the batch's lattices.
 hipError_t launch_batch_cell_stats(const SweepArgs *d_args, const int64_t *d_label_off, int n_lattices, int ndim,
-                                   size_t max_sites, int64_t max_bricks, size_t total_labels, int32_t *v_out,
-                                   int32_t *s_out, int32_t *ref, int64_t *cent, hipStream_t stream);
+                                   int64_t max_bricks, size_t total_labels, int32_t *v_out, int32_t *s_out, int32_t *ref,
+                                   int64_t *cent, hipStream_t stream);
 // One MCS of the serial CPM on every lattice of a batch (one wave each),
 // without the Act decay; counters: the exact buffer `parity`.
 hipError_t launch_serial_mcs(const SweepArgs *d_args, int n_lattices, int ndim, bool act, bool mirror, uint32_t mcs,
@@ -294,10 +294,15 @@ hipError_t launch_after_serial(const SweepArgs *d_args, const int64_t *d_label_o
 // one size, n_sites each, packed back to back).
 hipError_t launch_occupancy(const int32_t *lattices, int n_lattices, size_t n_sites, int32_t *counts,
                             hipStream_t st);
-// Workgroups of the centroid reductions over a lattice of dims L.
+// Workgroups of the reductions over a lattice of dims L.
 int64_t reduce_brick_count(const int *L, int ndim);
-hipError_t launch_count(const SweepArgs &a, int ndim, int32_t *v_out, int32_t *s_out, int stride,
-                        hipStream_t stream);
+// Volumes and surfaces, added to the outputs, and (ref != NULL) the cells'
+// lowest site indices.
+hipError_t launch_count(const SweepArgs &a, int ndim, int32_t *v_out, int32_t *s_out, int stride, hipStream_t stream,
+                        int32_t *ref = nullptr);
+// What the reductions add to, cleared: n labels each of v, s and ref, and
+// ndim centroid sums per label; any of them may be NULL.
+hipError_t launch_clear_stats(int32_t *v, int32_t *s, int32_t *ref, size_t n, int64_t *cent, int ndim, hipStream_t stream);
 // Stored words the sweep works on: the caller's int32 labels, the 16-bit
 // working copy, or the int32 lattice rewritten in place as packed words.
 enum Words { kWords32 = 0, kWords16 = 1, kWordsPacked = 2, kWordsPackedAct = 3 };
@@ -343,8 +348,9 @@ hipError_t launch_to_act16(const int32_t *lat, const uint8_t *act, uint16_t *wor
 hipError_t launch_count_above(const uint8_t *act, size_t n, int limit, int32_t *count, hipStream_t stream);
 hipError_t launch_from_act16(const uint16_t *words, int32_t *lat, uint8_t *act, size_t n, hipStream_t stream);
 hipError_t launch_act16_decay(uint16_t *words, size_t n, hipStream_t stream);
+// have_ref: `ref` holds the lowest sites already, and `out` is cleared.
 hipError_t launch_centroids(const SweepArgs &a, int ndim, int32_t n_cells, int32_t *ref,
-                            int64_t *out, hipStream_t stream, int words = kWords32);
+                            int64_t *out, hipStream_t stream, int words = kWords32, bool have_ref = false);
 // Persistence directions (x, y, z of each int4) into out, 3 x n_labels int32.
 hipError_t launch_copy_dirs(const int4 *pdir, int32_t n_labels, int32_t *out, hipStream_t stream);
 hipError_t launch_copy_counters(const int32_t *pairs, int32_t n_labels, int32_t *v_out,

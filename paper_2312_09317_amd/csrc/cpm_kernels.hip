@@ -8,22 +8,35 @@
 namespace cpm {
 namespace {
 
-// Per-workgroup label map in LDS: sums per cell label are combined in LDS
-// and flushed with one global atomic per label and workgroup.  A label that
-// finds no free slot within kProbe probes goes straight to global memory.
-constexpr int kMapSize = 1024;
+// Reductions over the cells of a lattice.  A workgroup takes a brick of it, a
+// thread kRun consecutive sites of one row, and adds once per run of one label
+// to a label map in LDS, which is flushed with one global atomic per label
+// and sum.  A label that finds no free slot within kProbe probes goes straight
+// to global memory.  Bricks rather than row strips keep the workgroups that
+// see one cell, and so the global atomics per cell, few.
+//
+//   kCount     volumes and surfaces, from the int32 labels; with `ref` also
+//              each cell's lowest site index
+//   kRef       the lowest site index alone
+//   kCentroid  coordinate sums, each site as its periodic image nearest to
+//              the cell's site of lowest index
+//
+// The counts are bound by instruction issue (two per compared pair, 27 pairs a
+// site in 3D).  With a map access per site, the neighbours' indices wrapped
+// one by one and a pass of its own for the lowest sites, 256^3 took 143 + 27
+// us and its centroids 59; now 82 and 35.  512 2D lattices of 51.6 million
+// sites in all: 517 + 118 + 252 us, now 192 + 116.
+constexpr int kMapSize = 512;
 constexpr int kProbe = 32;
-constexpr int kSitesPerThread = 16;
-constexpr int kSitesPerBlock = kBlock * kSitesPerThread;
+constexpr int kRun = 16;
 
-// Brick of the run-based reductions: kTX threads of kSitesPerThread sites
-// along x, kY rows, kZ planes (kTX * kY * kZ = kBlock).
+// Threads of a brick: kTX along x (kRun sites each), kY rows, kZ planes.
 template <int D>
 struct ReduceBrick {
     static constexpr int kTX = D == 3 ? 1 : 4;
     static constexpr int kY = D == 3 ? 16 : 64;
     static constexpr int kZ = D == 3 ? 16 : 1;
-    static constexpr int kX = kTX * kSitesPerThread;
+    static constexpr int kX = kTX * kRun;
     static_assert(kTX * kY * kZ == kBlock, "one thread per brick row segment");
 };
 
@@ -36,16 +49,19 @@ __host__ __device__ inline int64_t reduce_bricks(const int *L)
 
 enum ReduceMode { kCount = 0, kRef = 1, kCentroid = 2 };
 
+template <int MODE>
 struct LabelMap {
     int32_t key[kMapSize];
-    int32_t a[kMapSize];                // volume, or minimum site index
-    int32_t b[kMapSize];                // surface
-    unsigned long long c[kMapSize][3];  // centroid sums
+    int32_t v[MODE == kCount ? kMapSize : 1], s[MODE == kCount ? kMapSize : 1];
+    int32_t low[MODE == kCentroid ? 1 : kMapSize];                        // lowest site index
+    unsigned long long c[MODE == kCentroid ? 3 : 1][MODE == kCentroid ? kMapSize : 1];
 };
 
-__device__ __forceinline__ int map_slot(LabelMap &m, int label)
+template <int MODE>
+__device__ __forceinline__ int map_slot(LabelMap<MODE> &m, int label)
 {
-    uint32_t h = ((uint32_t)label * 2654435761u) & (kMapSize - 1);
+    uint32_t h = ((uint32_t)label * 2654435761u) >> 23;
+    static_assert(kMapSize == 1 << 9, "the hash is the product's upper 9 bits");
     for (int p = 0; p < kProbe; ++p) {
         const int k = atomicCAS(&m.key[h], -1, label);
         if (k == -1 || k == label) return (int)h;
@@ -54,8 +70,6 @@ __device__ __forceinline__ int map_slot(LabelMap &m, int label)
     return -1;
 }
 
-// The kSitesPerThread consecutive labels from site i0 (n of them valid),
-// vector loads where the row of them is whole and 16-byte aligned.
 // A label from an int32 lattice word: the label itself, or a packed word.
 template <int WORDS>
 __device__ __forceinline__ int word_label(int32_t v)
@@ -65,13 +79,15 @@ __device__ __forceinline__ int word_label(int32_t v)
     return v;
 }
 
+// The labels of the kRun consecutive sites from site i0 (n of them valid),
+// vector loads where the run is whole and 16-byte aligned.
 template <int WORDS>
-__device__ __forceinline__ void load_run_labels(const SweepArgs &a, int64_t i0, int n, int (&lab)[kSitesPerThread])
+__device__ __forceinline__ void load_run_labels(const SweepArgs &a, int64_t i0, int n, int *lab)
 {
-    static_assert(kSitesPerThread == 16, "vector loads below assume 16 sites per thread");
+    static_assert(kRun == 16, "vector loads below assume 16 sites per thread");
     if (WORDS == kWords16) {
         const uint16_t *src = reinterpret_cast<const uint16_t *>(a.cells) + i0;
-        if (n == kSitesPerThread && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
+        if (n == kRun && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
             const uint4 v[2] = {reinterpret_cast<const uint4 *>(src)[0], reinterpret_cast<const uint4 *>(src)[1]};
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
@@ -81,11 +97,11 @@ __device__ __forceinline__ void load_run_labels(const SweepArgs &a, int64_t i0, 
             }
         } else {
 #pragma unroll
-            for (int k = 0; k < kSitesPerThread; ++k) lab[k] = k < n ? label_of(src[k]) : 0;
+            for (int k = 0; k < kRun; ++k) lab[k] = k < n ? label_of(src[k]) : 0;
         }
     } else {
         const int32_t *src = a.lat + i0;
-        if (n == kSitesPerThread && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
+        if (n == kRun && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int4 v = reinterpret_cast<const int4 *>(src)[k];
@@ -96,119 +112,199 @@ __device__ __forceinline__ void load_run_labels(const SweepArgs &a, int64_t i0, 
             }
         } else {
 #pragma unroll
-            for (int k = 0; k < kSitesPerThread; ++k) lab[k] = k < n ? word_label<WORDS>(src[k]) : 0;
+            for (int k = 0; k < kRun; ++k) lab[k] = k < n ? word_label<WORDS>(src[k]) : 0;
         }
     }
 }
 
-// One workgroup's share of a reduction over lattice a, read from its int32
-// labels, its 16-bit working copy or its packed words (WORDS).  kCount
-// (int32 labels only): kSitesPerBlock sites
-// from `block`, thread t taking sites t, t + kBlock, ... (its neighbours'
-// reads coalesce).  kRef, kCentroid: brick `block` (ReduceBrick), thread t
-// taking kSitesPerThread consecutive sites of one row and touching the label
-// map once per run of one label: at the run's first site (the smallest index
-// of the run) for kRef, with the run's summed coordinates for kCentroid.
-// Bricks rather than row strips keep the workgroups that see one cell, and
-// so the global atomics per cell, few.
+// floor(n / d) for 0 <= n < 2^31 by the reciprocal of d in FP64, off by at
+// most one before the correction.
+__device__ __forceinline__ int div_index(int n, int d, double inv)
+{
+    const int q = (int)((double)n * inv), r = n - q * d;
+    return r < 0 ? q - 1 : r >= d ? q + 1 : q;
+}
+
+// p - r as the nearest periodic image on an axis of length L.
+__device__ __forceinline__ int nearest_image(int diff, int L)
+{
+    if (diff > L / 2) diff -= L;
+    if (diff < -(L - 1) / 2) diff += L;
+    return diff;
+}
+
+// One workgroup's share of a reduction over lattice a: brick `block`, read
+// from its int32 labels, its 16-bit working copy or its packed words (WORDS).
 template <int D, int MODE, int WORDS = kWords32>
 __device__ __forceinline__ void reduce_block(const SweepArgs &a, int64_t block, int32_t *v_out, int32_t *s_out,
                                              int stride, int32_t *ref, int64_t *cent)
 {
-    __shared__ LabelMap m;
+    __shared__ LabelMap<MODE> m;
     const int tid = threadIdx.x;
     for (int i = tid; i < kMapSize; i += kBlock) {
         m.key[i] = -1;
-        m.a[i] = MODE == kRef ? INT32_MAX : 0;
-        m.b[i] = 0;
-        m.c[i][0] = m.c[i][1] = m.c[i][2] = 0;
+        if (MODE == kCount) m.v[i] = m.s[i] = 0;
+        if (MODE != kCentroid) m.low[i] = INT32_MAX;
+        else m.c[0][i] = m.c[1][i] = m.c[2][i] = 0;
     }
     __syncthreads();
     const int L0 = a.L[0], L1 = a.L[1], L2 = a.L[2];
-    const int64_t n_sites = (int64_t)L0 * L1 * L2;
-    const int64_t base = block * kSitesPerBlock;
-    constexpr int NNB = D == 2 ? 8 : 26;
-    if (MODE == kCount) {
-        for (int j = 0; j < kSitesPerThread; ++j) {
-            const int64_t i = base + tid + (int64_t)j * kBlock;
-            if (i >= n_sites) break;
-            const int32_t c = a.lat[i];
-            if (c <= 0) continue;
-            const int x = (int)(i % L0), y = (int)((i / L0) % L1), z = (int)(i / ((int64_t)L0 * L1));
-            const int slot = map_slot(m, c);
-            int unlike = 0;
-#pragma unroll
-            for (int n = 0; n < NNB; ++n) {
-                const int u = wrap_once(x + nb_dx<D>(n), L0) +
-                              L0 * (wrap_once(y + nb_dy<D>(n), L1) + L1 * (D == 3 ? wrap_once(z + nb_dz<D>(n), L2) : 0));
-                unlike += a.lat[u] != c;
+    using B = ReduceBrick<D>;
+    const int nbx = (L0 + B::kX - 1) / B::kX, nby = (L1 + B::kY - 1) / B::kY;
+    const int bx = (int)(block % nbx), by = (int)((block / nbx) % nby), bz = (int)(block / ((int64_t)nbx * nby));
+    const int tx = tid % B::kTX, ty = (tid / B::kTX) % B::kY, tz = tid / (B::kTX * B::kY);
+    const int x = bx * B::kX + tx * kRun, y = by * B::kY + ty, z = bz * B::kZ + tz;
+    // 3D counts: the brick's labels with their neighbours, in LDS.  A row's
+    // 16 labels straight from global memory cost a lane a cache line of its
+    // own for each of nine rows: 241 us for 256^3.
+    constexpr int kBoxX = kRun + 2, kBoxY = B::kY + 2, kBoxZ = B::kZ + 2;
+    constexpr bool BOX = D == 3 && MODE == kCount;
+    __shared__ int32_t box[BOX ? kBoxX * kBoxY * kBoxZ : 1];
+    __shared__ struct {
+        int32_t lab[BOX ? 1 : kRun][kBlock];
+        uint16_t unlike[MODE == kCount ? kRun : 1][kBlock];
+    } runs;
+    if (BOX) {
+        const int x0 = bx * B::kX, y0 = by * B::kY - 1, z0 = bz * B::kZ - 1;
+        const bool vec = x0 + kRun <= L0 && L0 % 4 == 0 && (reinterpret_cast<uintptr_t>(a.lat) & 15) == 0;
+        auto row_of = [&](int r) {  // rows past the lattice's end are never used
+            const int ry = r % kBoxY, rz = r / kBoxY;
+            const int gy = y0 + ry < 0 ? L1 - 1 : (y0 + ry) % L1, gz = z0 + rz < 0 ? L2 - 1 : (z0 + rz) % L2;
+            return (gz * L1 + gy) * L0;
+        };
+        if (vec) {
+            // per row four vectors and the two labels beside them
+            for (int i = tid; i < 6 * kBoxY * kBoxZ; i += kBlock) {
+                const int r = i / 6, k = i - 6 * r, row = row_of(r);
+                int32_t *d = box + r * kBoxX;
+                if (k < 4) {
+                    const int4 v = *reinterpret_cast<const int4 *>(a.lat + row + x0 + 4 * k);
+                    d[4 * k + 1] = v.x;
+                    d[4 * k + 2] = v.y;
+                    d[4 * k + 3] = v.z;
+                    d[4 * k + 4] = v.w;
+                } else if (k == 4) {
+                    d[0] = a.lat[row + (x0 > 0 ? x0 - 1 : L0 - 1)];
+                } else {
+                    d[kRun + 1] = a.lat[row + (x0 + kRun < L0 ? x0 + kRun : 0)];
+                }
             }
-            if (slot >= 0) {
-                atomicAdd(&m.a[slot], 1);
-                atomicAdd(&m.b[slot], unlike);
-            } else {
-                atomicAdd(&v_out[(size_t)c * stride], 1);
-                atomicAdd(&s_out[(size_t)c * stride], unlike);
+        } else {
+            for (int i = tid; i < kBoxX * kBoxY * kBoxZ; i += kBlock) {
+                const int r = i / kBoxX, gx = x0 - 1 + i - r * kBoxX;
+                box[i] = a.lat[row_of(r) + (gx < 0 ? L0 - 1 : gx % L0)];
             }
         }
-    } else {
-        using B = ReduceBrick<D>;
-        const int nbx = (L0 + B::kX - 1) / B::kX, nby = (L1 + B::kY - 1) / B::kY;
-        const int bx = (int)(block % nbx), by = (int)((block / nbx) % nby), bz = (int)(block / ((int64_t)nbx * nby));
-        const int tx = tid % B::kTX, ty = (tid / B::kTX) % B::kY, tz = tid / (B::kTX * B::kY);
-        int x = bx * B::kX + tx * kSitesPerThread;
-        const int y = by * B::kY + ty, z = bz * B::kZ + tz;
-        if (x < L0 && y < L1 && z < L2) {
-            const int n = min(kSitesPerThread, L0 - x);
-            const int first = (z * L1 + y) * L0 + x;  // lattices hold fewer than 2^31 sites
-            int lab[kSitesPerThread];
+        __syncthreads();
+    }
+    if (x < L0 && y < L1 && z < L2) {
+        const int n = min(kRun, L0 - x);
+        const int first = (z * L1 + y) * L0 + x;  // lattices hold fewer than 2^31 sites
+        int lab[kRun];
+        if (BOX) {
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) lab[j] = box[((tz + 1) * kBoxY + ty + 1) * kBoxX + 1 + j];
+        } else {
             load_run_labels<WORDS>(a, first, n, lab);
-            int cur = INT32_MIN;  // label of the open run
-            int r[3] = {0, 0, 0};
-            int64_t acc[3] = {0, 0, 0};
-            auto flush = [&]() {
-                const int slot = map_slot(m, cur);
+        }
+        if (n < kRun) {
 #pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    if (slot >= 0) atomicAdd(&m.c[slot][d], (unsigned long long)acc[d]);
-                    else atomicAdd(reinterpret_cast<unsigned long long *>(&cent[(size_t)cur * D + d]),
-                                   (unsigned long long)acc[d]);
-                }
+            for (int j = 0; j < kRun; ++j)
+                if (j >= n) lab[j] = 0;  // past the row's end: medium
+        }
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < kRun; ++j) any |= lab[j] > 0;
+        int cnt[kRun];  // kCount: unlike neighbours
+        if (MODE == kCount && any) {
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) cnt[j] = 0;
+            const int xm = x > 0 ? x - 1 : L0 - 1, xp = x + n < L0 ? x + n : 0;
+            auto compare = [&](const int *u) {  // (a site never differs from itself)
+#pragma unroll
+                for (int j = 0; j < kRun; ++j) cnt[j] += (u[j] != lab[j]) + (u[j + 1] != lab[j]) + (u[j + 2] != lab[j]);
             };
-            const int L[3] = {L0, L1, L2};
+            if (D == 3) {
+#pragma unroll 1
+                for (int dz = 0; dz < 3; ++dz)
 #pragma unroll
-            for (int j = 0; j < kSitesPerThread; ++j) {
-                if (j < n) {
-                    const int c = lab[j];
-                    if (c != cur) {
-                        if (MODE == kCentroid && cur > 0) flush();
-                        cur = c;
-                        if (c > 0 && MODE == kRef) {
-                            const int slot = map_slot(m, c);
-                            if (slot >= 0) atomicMin(&m.a[slot], first + j);
-                            else atomicMin(&ref[c], first + j);
-                        } else if (c > 0) {
-                            const int r0 = ref[c];
-                            r[0] = r0 % L0;
-                            r[1] = (r0 / L0) % L1;
-                            r[2] = r0 / (L0 * L1);
-                            acc[0] = acc[1] = acc[2] = 0;
-                        }
-                    }
-                    if (MODE == kCentroid && c > 0) {
-                        const int p[3] = {x, y, z};
+                    for (int dy = 0; dy < 3; ++dy) compare(box + ((tz + dz) * kBoxY + ty + dy) * kBoxX);
+            } else {
+                int u[3][kRun + 2];
 #pragma unroll
-                        for (int d = 0; d < D; ++d) {
-                            int diff = p[d] - r[d];
-                            if (diff > L[d] / 2) diff -= L[d];
-                            if (diff < -(L[d] - 1) / 2) diff += L[d];
-                            acc[d] += r[d] + diff;
-                        }
+                for (int r = 0; r < 3; ++r) {  // all loads before the first use
+                    const int row = wrap_once(y + r - 1, L1) * L0;
+                    load_run_labels<WORDS>(a, (int64_t)row + x, n, u[r] + 1);
+                    u[r][0] = a.lat[row + xm];
+                    u[r][kRun + 1] = a.lat[row + xp];
+                }
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    if (n < kRun) {
+#pragma unroll
+                        for (int j = 0; j < kRun; ++j)
+                            if (j == n) u[r][j + 1] = u[r][kRun + 1];
                     }
-                    ++x;
+                    compare(u[r]);
                 }
             }
-            if (MODE == kCentroid && cur > 0) flush();
+        }
+        if (any) {
+            // the runs, one after another: as many rounds per wave as its
+            // busiest thread has runs, their labels and sums by index from LDS
+            uint32_t starts = 0, ends = 0;
+            int sum = 0;
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) {
+                if (!BOX) runs.lab[j][tid] = lab[j];
+                if (MODE == kCount) {
+                    sum += cnt[j];
+                    runs.unlike[j][tid] = (uint16_t)sum;  // of the run's sites up to j, and before it
+                }
+                starts |= (uint32_t)(lab[j] > 0 && (j == 0 || lab[j] != lab[j > 0 ? j - 1 : 0])) << j;
+                ends |= (uint32_t)(lab[j] > 0 && (j == kRun - 1 || lab[j] != lab[j < kRun - 1 ? j + 1 : j])) << j;
+            }
+            const double inv0 = 1.0 / (double)L0, inv1 = 1.0 / (double)L1;
+            while (ends) {
+                const int s = __ffs(starts) - 1, e = __ffs(ends) - 1, len = e - s + 1;
+                starts &= starts - 1;
+                ends &= ends - 1;
+                const int c = BOX ? box[((tz + 1) * kBoxY + ty + 1) * kBoxX + 1 + e] : runs.lab[e][tid];
+                const int slot = map_slot(m, c);
+                if (MODE == kCount) {
+                    const int unlike = runs.unlike[e][tid] - (s > 0 ? (int)runs.unlike[s > 0 ? s - 1 : 0][tid] : 0);
+                    if (slot >= 0) {
+                        atomicAdd(&m.v[slot], len);
+                        atomicAdd(&m.s[slot], unlike);
+                    } else {
+                        atomicAdd(&v_out[(size_t)c * stride], len);
+                        atomicAdd(&s_out[(size_t)c * stride], unlike);
+                    }
+                }
+                if (MODE == kRef || (MODE == kCount && ref)) {
+                    if (slot >= 0) atomicMin(&m.low[slot], first + s);
+                    else atomicMin(&ref[c], first + s);
+                }
+                if (MODE == kCentroid) {
+                    const int r0 = ref[c], q = div_index(r0, L0, inv0), rx = r0 - q * L0;
+                    const int rz = D == 3 ? div_index(q, L1, inv1) : 0, ry = q - rz * L1;
+                    // the images along the run are consecutive, unless the far
+                    // side of the lattice lies within it
+                    const int i0 = nearest_image(x + s - rx, L0), i1 = nearest_image(x + e - rx, L0);
+                    int64_t sx = (int64_t)len * i0 + len * (len - 1) / 2;
+                    if (i1 != i0 + len - 1) {
+                        sx = 0;
+                        for (int j = s; j <= e; ++j) sx += nearest_image(x + j - rx, L0);
+                    }
+                    const int64_t d[3] = {(int64_t)len * rx + sx, (int64_t)len * (ry + nearest_image(y - ry, L1)),
+                                          (int64_t)len * (rz + nearest_image(z - rz, L2))};
+#pragma unroll
+                    for (int k = 0; k < D; ++k) {
+                        if (slot >= 0) atomicAdd(&m.c[k][slot], (unsigned long long)d[k]);
+                        else atomicAdd(reinterpret_cast<unsigned long long *>(&cent[(size_t)c * D + k]), (unsigned long long)d[k]);
+                    }
+                }
+            }
         }
     }
     __syncthreads();
@@ -216,14 +312,14 @@ __device__ __forceinline__ void reduce_block(const SweepArgs &a, int64_t block, 
         const int c = m.key[h];
         if (c < 0) continue;
         if (MODE == kCount) {
-            atomicAdd(&v_out[(size_t)c * stride], m.a[h]);
-            atomicAdd(&s_out[(size_t)c * stride], m.b[h]);
-        } else if (MODE == kRef) {
-            atomicMin(&ref[c], m.a[h]);
-        } else {
+            atomicAdd(&v_out[(size_t)c * stride], m.v[h]);
+            atomicAdd(&s_out[(size_t)c * stride], m.s[h]);
+        }
+        if (MODE == kRef || (MODE == kCount && ref)) atomicMin(&ref[c], m.low[h]);
+        if (MODE == kCentroid) {
 #pragma unroll
             for (int d = 0; d < D; ++d)
-                atomicAdd(reinterpret_cast<unsigned long long *>(&cent[(size_t)c * D + d]), m.c[h][d]);
+                atomicAdd(reinterpret_cast<unsigned long long *>(&cent[(size_t)c * D + d]), m.c[d][h]);
         }
     }
 }
@@ -244,13 +340,26 @@ __global__ void __launch_bounds__(kBlock) batch_reduce_kernel(const SweepArgs *a
                                                               int64_t *cent)
 {
     const SweepArgs &a = args[blockIdx.y];
-    const int64_t n_sites = (int64_t)a.L[0] * a.L[1] * a.L[2];
-    if (MODE == kCount ? (int64_t)blockIdx.x * kSitesPerBlock >= n_sites : blockIdx.x >= reduce_bricks<D>(a.L))
-        return;  // uniform over the block
+    if (blockIdx.x >= reduce_bricks<D>(a.L)) return;  // uniform over the block
     const int64_t o = label_off[blockIdx.y];
     reduce_block<D, MODE>(a, blockIdx.x, v_out ? v_out + o : nullptr, s_out ? s_out + o : nullptr, 1,
                           ref ? ref + o : nullptr, cent ? cent + o * D : nullptr);
 }
+
+// The reductions' outputs before they are added to: sums 0 (volumes and
+// surfaces, n labels each; n_cent words of centroid sums), lowest sites none.
+__global__ void clear_stats_kernel(int32_t *v, int32_t *s, int32_t *ref, size_t n, int64_t *cent, size_t n_cent)
+{
+    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) {
+        if (v) v[i] = 0;
+        if (s) s[i] = 0;
+        if (ref) ref[i] = INT32_MAX;
+    }
+    if (cent && i < n_cent) cent[i] = 0;
+}
+
+constexpr int kContactSites = 16 * kBlock;  // sites per workgroup of contact_kernel
 
 // Ordered Moore pairs (x, y) of different labels, neither an obstacle, counted
 // by (type of x, type of y); the medium is type 0.  Per-wave LDS histograms,
@@ -265,9 +374,9 @@ __global__ void __launch_bounds__(kBlock) contact_kernel(SweepArgs a, unsigned l
     __syncthreads();
     const int L0 = a.L[0], L1 = a.L[1], L2 = a.L[2];
     const int64_t n_sites = (int64_t)L0 * L1 * L2;
-    const int64_t base = (int64_t)blockIdx.x * kSitesPerBlock;
+    const int64_t base = (int64_t)blockIdx.x * kContactSites;
     constexpr int NNB = D == 2 ? 8 : 26;
-    for (int j = 0; j < kSitesPerThread; ++j) {
+    for (int j = 0; j < 16; ++j) {
         const int64_t i = base + tid + (int64_t)j * kBlock;
         if (i >= n_sites) break;
         const int32_t c = a.lat[i];
@@ -451,15 +560,20 @@ hipError_t launch_fill_i32(int32_t *p, int32_t value, size_t n, hipStream_t stre
     return hipGetLastError();
 }
 
-hipError_t launch_count(const SweepArgs &a, int ndim, int32_t *v_out, int32_t *s_out, int stride,
-                        hipStream_t stream)
+hipError_t launch_clear_stats(int32_t *v, int32_t *s, int32_t *ref, size_t n, int64_t *cent, int ndim, hipStream_t stream)
 {
-    const size_t n = (size_t)a.L[0] * a.L[1] * a.L[2];
-    const unsigned grid = (unsigned)((n + kSitesPerBlock - 1) / kSitesPerBlock);
+    clear_stats_kernel<<<blocks_for(cent ? n * ndim : n), kBlock, 0, stream>>>(v, s, ref, n, cent, n * ndim);
+    return hipGetLastError();
+}
+
+hipError_t launch_count(const SweepArgs &a, int ndim, int32_t *v_out, int32_t *s_out, int stride, hipStream_t stream,
+                        int32_t *ref)
+{
+    const unsigned grid = (unsigned)reduce_brick_count(a.L, ndim);
     if (ndim == 2)
-        reduce_kernel<2, kCount><<<grid, kBlock, 0, stream>>>(a, v_out, s_out, stride, nullptr, nullptr);
+        reduce_kernel<2, kCount><<<grid, kBlock, 0, stream>>>(a, v_out, s_out, stride, ref, nullptr);
     else
-        reduce_kernel<3, kCount><<<grid, kBlock, 0, stream>>>(a, v_out, s_out, stride, nullptr, nullptr);
+        reduce_kernel<3, kCount><<<grid, kBlock, 0, stream>>>(a, v_out, s_out, stride, ref, nullptr);
     return hipGetLastError();
 }
 
@@ -468,7 +582,7 @@ hipError_t launch_contacts(const SweepArgs &a, int ndim, int n_types, int64_t *o
     hipError_t e = launch_fill_i32(reinterpret_cast<int32_t *>(out), 0, (size_t)n_types * n_types * 2, stream);
     if (e != hipSuccess) return e;
     const size_t n = (size_t)a.L[0] * a.L[1] * a.L[2];
-    const unsigned grid = (unsigned)((n + kSitesPerBlock - 1) / kSitesPerBlock);
+    const unsigned grid = (unsigned)((n + kContactSites - 1) / kContactSites);
     auto *o = reinterpret_cast<unsigned long long *>(out);
     if (ndim == 2) contact_kernel<2><<<grid, kBlock, 0, stream>>>(a, o, n_types);
     else contact_kernel<3><<<grid, kBlock, 0, stream>>>(a, o, n_types);
@@ -489,16 +603,16 @@ hipError_t launch_act_decay(uint8_t *act, size_t n, hipStream_t stream)
 }
 
 hipError_t launch_centroids(const SweepArgs &a, int ndim, int32_t n_cells, int32_t *ref, int64_t *out,
-                            hipStream_t stream, int words)
+                            hipStream_t stream, int words, bool have_ref)
 {
-    const unsigned grid = (unsigned)(ndim == 2 ? reduce_bricks<2>(a.L) : reduce_bricks<3>(a.L));
-    hipError_t e = launch_fill_i32(ref, INT32_MAX, (size_t)n_cells + 1, stream);
-    if (e != hipSuccess) return e;
-    e = launch_fill_i32(reinterpret_cast<int32_t *>(out), 0, ((size_t)n_cells + 1) * ndim * 2, stream);
-    if (e != hipSuccess) return e;
+    const unsigned grid = (unsigned)reduce_brick_count(a.L, ndim);
+    if (!have_ref) {
+        const hipError_t e = launch_clear_stats(nullptr, nullptr, ref, (size_t)n_cells + 1, out, ndim, stream);
+        if (e != hipSuccess) return e;
+    }
     auto run = [&](auto d_tag, auto w_tag) {
         constexpr int D = decltype(d_tag)::value, W = decltype(w_tag)::value;
-        reduce_kernel<D, kRef, W><<<grid, kBlock, 0, stream>>>(a, nullptr, nullptr, 0, ref, nullptr);
+        if (!have_ref) reduce_kernel<D, kRef, W><<<grid, kBlock, 0, stream>>>(a, nullptr, nullptr, 0, ref, nullptr);
         reduce_kernel<D, kCentroid, W><<<grid, kBlock, 0, stream>>>(a, nullptr, nullptr, 0, ref, out);
     };
     using D2 = std::integral_constant<int, 2>;
@@ -560,26 +674,19 @@ hipError_t launch_copy_dirs(const int4 *pdir, int32_t n_labels, int32_t *out, hi
 }
 
 hipError_t launch_batch_cell_stats(const SweepArgs *d_args, const int64_t *d_label_off, int n_lattices, int ndim,
-                                   size_t max_sites, int64_t max_bricks, size_t total_labels, int32_t *v_out,
-                                   int32_t *s_out, int32_t *ref, int64_t *cent, hipStream_t stream)
+                                   int64_t max_bricks, size_t total_labels, int32_t *v_out, int32_t *s_out, int32_t *ref,
+                                   int64_t *cent, hipStream_t stream)
 {
-    const dim3 grid((unsigned)((max_sites + kSitesPerBlock - 1) / kSitesPerBlock), (unsigned)n_lattices);
-    const dim3 grid_b((unsigned)max_bricks, (unsigned)n_lattices);
-    hipError_t e;
-    if ((e = launch_fill_i32(v_out, 0, total_labels, stream)) != hipSuccess) return e;
-    if ((e = launch_fill_i32(s_out, 0, total_labels, stream)) != hipSuccess) return e;
-    if (ndim == 2) batch_reduce_kernel<2, kCount><<<grid, kBlock, 0, stream>>>(d_args, d_label_off, v_out, s_out, nullptr, nullptr);
-    else batch_reduce_kernel<3, kCount><<<grid, kBlock, 0, stream>>>(d_args, d_label_off, v_out, s_out, nullptr, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess || !cent) return e;
-    if ((e = launch_fill_i32(ref, INT32_MAX, total_labels, stream)) != hipSuccess) return e;
-    if ((e = launch_fill_i32(reinterpret_cast<int32_t *>(cent), 0, total_labels * ndim * 2, stream)) != hipSuccess)
-        return e;
+    const dim3 grid((unsigned)max_bricks, (unsigned)n_lattices);
+    if (!cent) ref = nullptr;  // the lowest sites are the centroids' references
+    const hipError_t e = launch_clear_stats(v_out, s_out, ref, total_labels, cent, ndim, stream);
+    if (e != hipSuccess) return e;
     if (ndim == 2) {
-        batch_reduce_kernel<2, kRef><<<grid_b, kBlock, 0, stream>>>(d_args, d_label_off, nullptr, nullptr, ref, nullptr);
-        batch_reduce_kernel<2, kCentroid><<<grid_b, kBlock, 0, stream>>>(d_args, d_label_off, nullptr, nullptr, ref, cent);
+        batch_reduce_kernel<2, kCount><<<grid, kBlock, 0, stream>>>(d_args, d_label_off, v_out, s_out, ref, nullptr);
+        if (cent) batch_reduce_kernel<2, kCentroid><<<grid, kBlock, 0, stream>>>(d_args, d_label_off, nullptr, nullptr, ref, cent);
     } else {
-        batch_reduce_kernel<3, kRef><<<grid_b, kBlock, 0, stream>>>(d_args, d_label_off, nullptr, nullptr, ref, nullptr);
-        batch_reduce_kernel<3, kCentroid><<<grid_b, kBlock, 0, stream>>>(d_args, d_label_off, nullptr, nullptr, ref, cent);
+        batch_reduce_kernel<3, kCount><<<grid, kBlock, 0, stream>>>(d_args, d_label_off, v_out, s_out, ref, nullptr);
+        if (cent) batch_reduce_kernel<3, kCentroid><<<grid, kBlock, 0, stream>>>(d_args, d_label_off, nullptr, nullptr, ref, cent);
     }
     return hipGetLastError();
 }
