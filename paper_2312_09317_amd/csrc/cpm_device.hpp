@@ -159,7 +159,10 @@ struct ThrTables {
     int n_ti;
 };
 
-// Accept iff q <= 0 or u < floor(TI[h] TM[m] TL[l] / 2^64), q = h*2^16 + m*2^8 + l.
+__device__ __forceinline__ int64_t mul32(int32_t a, int32_t b) { return (int64_t)a * b; }
+
+// Accept iff q <= 0 or u < floor(TI[h] TM[m] TL[l] / 2^64), q = h*2^16 + m*2^8 + l,
+// by 32-bit products: an entry of index 0 is 2^32, every other one below it.
 // The three table entries are read in one round (indices clamped into the
 // tables) and the decision is taken without branches: the entries a case
 // does not use are ignored.
@@ -167,18 +170,17 @@ __device__ __forceinline__ bool metropolis32(const ThrTables &tb, int64_t q, uin
 {
     const uint64_t h = (uint64_t)q >> 16;
     const bool in = q > 0 && h < (uint64_t)tb.n_ti;
-    const int mm = (int)((q >> 8) & 255), ll = (int)(q & 255);
-    const uint64_t two32 = (uint64_t)1 << 32;
-    const uint32_t ti_w = tb.ti[in ? h : 0], tm_w = tb.tm[mm], tl_w = tb.tl[ll];
+    const uint32_t mm = (uint32_t)(q >> 8) & 255u, ll = (uint32_t)q & 255u;
+    const uint32_t ti = tb.ti[in ? (uint32_t)h : 0u], tm = tb.tm[mm], tl = tb.tl[ll];
     // an empty asm that takes the three entries keeps the compiler from
     // moving the loads of tm and tl into the branch that uses them
-    asm volatile("" ::"v"(ti_w), "v"(tm_w), "v"(tl_w));
-    const uint64_t ti_e = ti_w, tm_e = tm_w, tl_e = tl_w;
-    const uint64_t ti = h == 0 ? two32 : ti_e;
-    const uint64_t tm = mm ? tm_e : two32, tl = ll ? tl_e : two32;
-    // tm * tl < 2^64 whenever (mm, ll) != (0, 0), the only case it is used
-    const uint64_t thr = (q & 0xFFFF) == 0 ? ti : __umul64hi(ti, tm * tl);
-    return (q <= 0) | (in & ((uint64_t)u < thr));
+    asm volatile("" ::"v"(ti), "v"(tm), "v"(tl));
+    const uint64_t p = mm == 0 ? (uint64_t)tl << 32 : ll == 0 ? (uint64_t)tm << 32 : (uint64_t)tm * tl;
+    const uint32_t hi = (uint32_t)(p >> 32), lo = (uint32_t)p;
+    const uint64_t prod = (uint64_t)ti * hi + (((uint64_t)ti * lo) >> 32);
+    const uint32_t thr = h == 0 ? hi : (uint32_t)(prod >> 32);
+    // (mm, ll) = (0, 0): TI itself, whose index is not 0 then, as q > 0
+    return (q <= 0) | (in & (u < ((q & 0xFFFF) == 0 ? ti : thr)));
 }
 
 // exp(l * 2^-24) in 2^16 fixed point, floor-composed from the split tables.

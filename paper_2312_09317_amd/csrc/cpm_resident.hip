@@ -108,24 +108,6 @@ __device__ __forceinline__ void add_copy(int2 *pairs, int4 r)
     if (r.y >= 1) add_pair(pairs, r.y, 1, r.w);
 }
 
-__device__ __forceinline__ int64_t mul32(int32_t a, int32_t b) { return (int64_t)a * b; }
-
-// metropolis32 with 32-bit products: thr = floor(TI TM TL / 2^64).
-__device__ __forceinline__ bool metropolis_lds(const ThrTables &tb, int64_t q, uint32_t u)
-{
-    const uint64_t h = (uint64_t)q >> 16;
-    const bool in = q > 0 && h < (uint64_t)tb.n_ti;
-    const uint32_t mm = (uint32_t)(q >> 8) & 255u, ll = (uint32_t)q & 255u;
-    const uint32_t ti = tb.ti[in ? (uint32_t)h : 0u], tm = tb.tm[mm], tl = tb.tl[ll];
-    // TM TL, a factor of index 0 being 2^32
-    const uint64_t p = mm == 0 ? (uint64_t)tl << 32 : ll == 0 ? (uint64_t)tm << 32 : (uint64_t)tm * tl;
-    const uint32_t hi = (uint32_t)(p >> 32), lo = (uint32_t)p;
-    const uint64_t prod = (uint64_t)ti * hi + (((uint64_t)ti * lo) >> 32);
-    const uint32_t thr = h == 0 ? hi : (uint32_t)(prod >> 32);
-    // (mm, ll) = (0, 0): TI itself (never 2^32 here: q > 0)
-    return (q <= 0) | (in & (u < ((q & 0xFFFF) == 0 ? ti : thr)));
-}
-
 // exp_log24 of a mean logarithm ell <= ln(255), 2^16 fixed point.
 __device__ __forceinline__ uint32_t exp_act(const ActLds &t, uint32_t ell)
 {
@@ -632,7 +614,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
                 q -= mul32(sh.lam_p[ts], u[0] * pd.x + u[1] * pd.y + (D == 3 ? u[2] * pd.z : 0)) >> 28;
             if (a.chem) q -= mul32(sh.lam_c[ts], u[0] * c[0] + u[1] * c[1] + (D == 3 ? u[2] * c[2] : 0)) >> 28;
         }
-        if (!metropolis_lds(tb, q, d.u2)) return;
+        if (!metropolis32(tb, q, d.u2)) return;
         ++my_accepted;
         uint32_t na = 0;
         if (ACT && ls >= 1 && es.max_act > 0) na = (uint32_t)es.max_act & 255u;

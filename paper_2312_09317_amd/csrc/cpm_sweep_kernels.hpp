@@ -92,6 +92,59 @@ struct LdsMap {
     __device__ __forceinline__ int at(int vx, int vy, int vz) const { return x(vx) + row(vy, vz); }
 };
 
+// The words of a site's Moore neighbourhood in place (global memory), the
+// site itself left out.  16-bit words in 3D: per row one load of 8 bytes from
+// the 4-byte boundary at or before x - 1, moved into the row at its ends,
+// where the word across the periodic boundary is loaded by itself.  Attempts
+// are scattered, so every lane of a load costs the vector cache a line of its
+// own: 9 loads instead of 26.  With 32-bit words (three of them per row, their
+// registers spilling) and in 2D (3 loads for 8) it measured slower, 17.3 vs
+// 14.8 ms for 2 MCS of 512^3 tissue.
+template <typename Cell, int D, typename Map>
+__device__ __forceinline__ void neighbour_words(const Cell *lab, const Map &map, int x, int y, int z, Cell *w)
+{
+    constexpr int NNB = D == 2 ? 8 : 26;
+    const int L0 = map.L0;
+    if (D == 2 || sizeof(Cell) != 2 || L0 < 4) {  // uniform
+#pragma unroll
+        for (int n = 0; n < NNB; ++n) w[n] = lab[map.at(x + nb_dx<D>(n), y + nb_dy<D>(n), z + nb_dz<D>(n))];
+        return;
+    }
+    constexpr int kRows = 9, kMid = 4;
+    x = map.x(x);  // a source may lie across the boundary
+    const bool lo = x == 0, hi = x == L0 - 1;
+    const int start = min(lo ? 0 : (x - 1) & ~1, L0 - 4), o = x - start;  // o in 0..3; rows have even length
+    uint64_t v[kRows];
+    int row[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        row[r] = map.row(y + r % 3 - 1, z + r / 3 - 1);
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(lab + row[r] + start);
+        v[r] = (uint64_t)p[0] | ((uint64_t)p[1] << 32);
+    }
+    Cell t[kRows][3];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const uint64_t s = lo ? v[r] << 16 : v[r] >> (16 * (o - 1));
+        t[r][0] = (Cell)(s & 0xFFFFu);
+        t[r][1] = (Cell)((s >> 16) & 0xFFFFu);
+        t[r][2] = (Cell)((s >> 32) & 0xFFFFu);
+    }
+    if (lo || hi) {
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const Cell e = lab[row[r] + (lo ? L0 - 1 : 0)];
+            t[r][0] = lo ? e : t[r][0];
+            t[r][2] = hi ? e : t[r][2];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (r != kMid || k != 1) w[3 * r + k - (3 * r + k > 3 * kMid + 1 ? 1 : 0)] = t[r][k];
+}
+
 // The mean of ln(activity) (2^-24 units) over a site and its Moore
 // neighbours of the same cell (the exponent of eq. 8), from words (and
 // activities) already loaded; `dead` when any of those activities is 0.
@@ -134,12 +187,10 @@ __device__ __forceinline__ int64_t gm_lds(const DeviceModel *m, const int64_t *l
         // activities) in one round, then the masked sums
         Cell w[NNB];
         uint32_t av[NNB];
+        neighbour_words<Cell, D>(lab, map, x, y, z, w);
 #pragma unroll
-        for (int n = 0; n < NNB; ++n) {
-            const int u = map.at(x + nb_dx<D>(n), y + nb_dy<D>(n), z + nb_dz<D>(n));
-            w[n] = lab[u];
-            av[n] = WordAct<Cell>::kIn ? 0u : (uint32_t)lact[u];
-        }
+        for (int n = 0; n < NNB; ++n)
+            av[n] = WordAct<Cell>::kIn ? 0u : (uint32_t)lact[map.at(x + nb_dx<D>(n), y + nb_dy<D>(n), z + nb_dz<D>(n))];
         bool dead;
         const uint32_t ell = mean_log_act<Cell, NNB>(lg, a0, w, av, cell, dead);
         return dead ? 0 : exp_log24(m, ell);
@@ -164,7 +215,7 @@ __device__ __forceinline__ int64_t gm_lds(const DeviceModel *m, const int64_t *l
 
 // J rows of the medium type and of the single cell type (when all cells share one type).
 struct JRows {
-    int64_t cc, cm, co, mc, mm, mo;
+    int32_t cc, cm, co, mc, mm, mo;  // |J| < 2^15: each entry fits 32 bits
 };
 
 // Per-workgroup LDS copies of the model tables an attempt reads: J
@@ -191,20 +242,19 @@ __device__ __forceinline__ bool evaluate_nb(const A &a, const ThrTables &tb, con
     constexpr bool kIn = WordAct<Cell>::kIn;
     const DeviceModel *m = plain(a.model);
     const TypeParams *tp = st.tp;
-    // In place (global memory), the target's neighbourhood comes first, in
-    // a block without branches, so that it is read in one round (several
-    // cell types, or the Act term, whose target mean reuses it); staged
-    // layouts read LDS as they go.  The source's neighbourhood (Act) is read
+    // In place (global memory), the target's neighbourhood comes first, so
+    // that it is read in one round (several cell types, 16-bit words in 3D,
+    // or the Act term, whose target mean reuses it); staged layouts read LDS
+    // as they go.  The source's neighbourhood (Act) is read
     // only for a motile source, in its own round: reading it with the
     // target's measured slower (registers).
-    constexpr bool GROUP = LAYOUT == kDirect && (!SINGLE || ACT);
+    constexpr bool GROUP = LAYOUT == kDirect && (!SINGLE || ACT || (D == 3 && sizeof(Cell) == 2));
     constexpr bool GACT = GROUP && ACT;
     Cell nw[NNB];
     uint32_t nav[GACT && !kIn ? NNB : 1];
     uint32_t ca_t = 0;
     if (GROUP) {
-#pragma unroll
-        for (int n = 0; n < NNB; ++n) nw[n] = nbl(n);
+        neighbour_words<Cell, D>(lab, map, tx_, ty_, tz_, nw);
         if (GACT) {
             ca_t = act_at(lab, lact, map.at(tx_, ty_, tz_));
             if (!kIn) {
@@ -215,7 +265,7 @@ __device__ __forceinline__ bool evaluate_nb(const A &a, const ThrTables &tb, con
         }
     }
     int k_old = 0, k_new = 0;
-    int n_cell = 0, n_med = 0, n_obs = 0;
+    int n_cell = 0, n_med = 0;
     int64_t adh = 0;
 #pragma unroll
     for (int n = 0; n < NNB; ++n) {
@@ -226,7 +276,6 @@ __device__ __forceinline__ bool evaluate_nb(const A &a, const ThrTables &tb, con
         if (SINGLE) {
             n_cell += lu > 0;
             n_med += lu == 0;
-            n_obs += lu < 0;
         } else if (GROUP) {
             // every J entry read, the ones of like labels masked
             const int tu = type_of_word(a, word, lu);
@@ -240,10 +289,13 @@ __device__ __forceinline__ bool evaluate_nb(const A &a, const ThrTables &tb, con
     }
     if (SINGLE) {
         // neighbours unlike the label, weighted by J(label type, their type)
-        const int64_t cs = n_cell - (ls > 0 ? k_new : 0), ms = n_med - (ls == 0 ? k_new : 0);
-        const int64_t ct = n_cell - (lt > 0 ? k_old : 0), mt = n_med - (lt == 0 ? k_old : 0);
-        adh = (ls > 0 ? jr.cc * cs + jr.cm * ms + jr.co * n_obs : jr.mc * cs + jr.mm * ms + jr.mo * n_obs) -
-              (lt > 0 ? jr.cc * ct + jr.cm * mt + jr.co * n_obs : jr.mc * ct + jr.mm * mt + jr.mo * n_obs);
+        const int n_obs = NNB - n_cell - n_med;
+        const int cs = n_cell - (ls > 0 ? k_new : 0), ms = n_med - (ls == 0 ? k_new : 0);
+        const int ct = n_cell - (lt > 0 ? k_old : 0), mt = n_med - (lt == 0 ? k_old : 0);
+        const auto row = [&](bool cell, int c, int m) {
+            return mul32(cell ? jr.cc : jr.mc, c) + mul32(cell ? jr.cm : jr.mm, m) + mul32(cell ? jr.co : jr.mo, n_obs);
+        };
+        adh = row(ls > 0, cs, ms) - row(lt > 0, ct, mt);
     }
     const int64_t dso = 2 * k_old - NNB;
     const int64_t dsn = NNB - 2 * k_new;
@@ -567,7 +619,8 @@ __device__ __forceinline__ void sweep_tile(const A &a, int tile, uint32_t mcs, u
         if (SINGLE) {
             const int64_t *J = model->J;
             const int tc = a.single_type, to = a.obstacle_type;
-            jr = JRows{J[tc * kMaxTypes + tc], J[tc * kMaxTypes], J[tc * kMaxTypes + to], J[tc], J[0], J[to]};
+            jr = JRows{(int32_t)J[tc * kMaxTypes + tc], (int32_t)J[tc * kMaxTypes], (int32_t)J[tc * kMaxTypes + to],
+                       (int32_t)J[tc], (int32_t)J[0], (int32_t)J[to]};
         }
         if (mine) {
             draw(tid, 0, ttx, tty, ttz, ssx, ssy, ssz, u2, area_id);
@@ -780,8 +833,8 @@ __device__ __forceinline__ void sweep_tile(const A &a, int tile, uint32_t mcs, u
     if (SINGLE) {
         const int64_t *J = model->J;
         const int tc = a.single_type, to = a.obstacle_type;
-        jr = JRows{J[tc * kMaxTypes + tc], J[tc * kMaxTypes], J[tc * kMaxTypes + to],
-                   J[tc], J[0], J[to]};
+        jr = JRows{(int32_t)J[tc * kMaxTypes + tc], (int32_t)J[tc * kMaxTypes], (int32_t)J[tc * kMaxTypes + to],
+                   (int32_t)J[tc], (int32_t)J[0], (int32_t)J[to]};
     }
     if (K1) {
         draw_k1();
@@ -922,7 +975,7 @@ struct PackedWaves {
     static constexpr bool kWordAct = std::is_same<Word, char32_t>::value;
     static constexpr int value =
         !K1 ? (ACT && (D == 3 || (SINGLE && EXT)) ? 3 : 4)
-        : D == 3 && LAYOUT == kDirect && !SINGLE ? (kWordAct ? CPM_PACKED_WAVES_3D : ACT ? 4 : 6)
+        : D == 3 && LAYOUT == kDirect && !SINGLE ? (kWordAct ? CPM_PACKED_WAVES_3D : ACT ? (EXT ? 3 : 4) : 6)
         : D == 3 && ACT ? (SINGLE ? 5 : 6)
         : D == 3 && EXT ? 6
         : D == 2 && ACT && (EXT || (LAYOUT == kDirect && !kWordAct)) ? 6
