@@ -359,46 +359,91 @@ __global__ void clear_stats_kernel(int32_t *v, int32_t *s, int32_t *ref, size_t 
     if (cent && i < n_cent) cent[i] = 0;
 }
 
-constexpr int kContactSites = 16 * kBlock;  // sites per workgroup of contact_kernel
-
 // Ordered Moore pairs (x, y) of different labels, neither an obstacle, counted
-// by (type of x, type of y); the medium is type 0.  Per-wave LDS histograms,
-// one 64-bit global atomic per bin and workgroup.
+// by (type of x, type of y); the medium is type 0.  Each unordered pair is met
+// once, from the site whose neighbour lies ahead in x, y or z, and counted
+// both ways at the end.  A thread compares the kRun sites of its brick row
+// with the rows ahead; the few pairs that differ go to a queue of the wave,
+// which looks up their types 64 at a time: looked up where found, one lane
+// in twenty at a time, they took 69 us at 2048^2, now 25.
 template <int D>
 __global__ void __launch_bounds__(kBlock) contact_kernel(SweepArgs a, unsigned long long *out, int n_types)
 {
-    constexpr int kBins = kMaxTypes * kMaxTypes;
-    __shared__ uint32_t hist[kBlock / 64][kBins];
-    const int tid = threadIdx.x, wave = tid >> 6;
-    for (int i = tid; i < (kBlock / 64) * kBins; i += kBlock) (&hist[0][0])[i] = 0;
+    constexpr int kBins = kMaxTypes * kMaxTypes, kCopies = 16, kQueued = 128;
+    __shared__ uint32_t hist[kCopies][kBins];  // by lane, to spread the updates of one bin
+    __shared__ int2 queue[kBlock / 64][kQueued];
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < kCopies * kBins; i += kBlock) (&hist[0][0])[i] = 0;
     __syncthreads();
+    using B = ReduceBrick<D>;
     const int L0 = a.L[0], L1 = a.L[1], L2 = a.L[2];
-    const int64_t n_sites = (int64_t)L0 * L1 * L2;
-    const int64_t base = (int64_t)blockIdx.x * kContactSites;
-    constexpr int NNB = D == 2 ? 8 : 26;
-    for (int j = 0; j < 16; ++j) {
-        const int64_t i = base + tid + (int64_t)j * kBlock;
-        if (i >= n_sites) break;
-        const int32_t c = a.lat[i];
-        if (c < 0) continue;
-        const int tc = c == 0 ? 0 : a.cell_type[c];
-        const int x = (int)(i % L0), y = (int)((i / L0) % L1), z = (int)(i / ((int64_t)L0 * L1));
+    const int nbx = (L0 + B::kX - 1) / B::kX, nby = (L1 + B::kY - 1) / B::kY;
+    const int bx = (int)(blockIdx.x % nbx), by = (int)((blockIdx.x / nbx) % nby), bz = (int)(blockIdx.x / ((int64_t)nbx * nby));
+    const int x = bx * B::kX + tid % B::kTX * kRun, y = by * B::kY + (tid / B::kTX) % B::kY, z = bz * B::kZ + tid / (B::kTX * B::kY);
+    const bool in = x < L0 && y < L1 && z < L2;
+    const int n = in ? min(kRun, L0 - x) : 0;
+    const int xm = x > 0 ? x - 1 : L0 - 1, xp = x + n < L0 ? x + n : 0;
+    int2 *q = queue[tid >> 6];
+    int queued = 0;  // of the wave
+    auto count = [&](int first, int entries) {
+        if (lane < entries) {
+            const int2 e = q[first + lane];
+            const int tx = e.x == 0 ? 0 : a.cell_type[e.x], ty = e.y == 0 ? 0 : a.cell_type[e.y];
+            atomicAdd(&hist[lane % kCopies][tx * kMaxTypes + ty], 1u);
+        }
+    };
+    auto pair = [&](bool valid, int c, int u) {
+        const bool differ = valid && c != u && c >= 0 && u >= 0;
+        const uint64_t mask = __ballot(differ);
+        if (mask == 0) return;
+        if (differ)
+            q[queued + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] =
+                make_int2(c, u);
+        queued += (int)__popcll(mask);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (queued >= 64) {
+            queued -= 64;
+            count(queued, 64);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    };
+    int lab[kRun + 1];
+    auto load_row = [&](int row, int *u) {  // n labels from x, and the one beyond them
+        load_run_labels<kWords32>(a, (int64_t)row + x, n, u);
+        u[kRun] = a.lat[row + xp];
+        if (n < kRun) {
 #pragma unroll
-        for (int n = 0; n < NNB; ++n) {
-            const int u = wrap_once(x + nb_dx<D>(n), L0) +
-                          L0 * (wrap_once(y + nb_dy<D>(n), L1) + L1 * (D == 3 ? wrap_once(z + nb_dz<D>(n), L2) : 0));
-            const int32_t lu = a.lat[u];
-            if (lu == c || lu < 0) continue;
-            const int tu = lu == 0 ? 0 : a.cell_type[lu];
-            atomicAdd(&hist[wave][tc * kMaxTypes + tu], 1u);
+            for (int j = 0; j < kRun; ++j)
+                if (j == n) u[j] = u[kRun];
+        }
+    };
+    if (in) load_row((z * L1 + y) * L0, lab);
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) pair(j < n, lab[j], lab[j + 1]);
+    // the rows ahead: y + 1, and in 3D the three rows of z + 1
+#pragma unroll 1
+    for (int r = 0; r < (D == 3 ? 4 : 1); ++r) {
+        int u[kRun + 1], before = 0;
+        if (in) {
+            const int gy = wrap_once(r == 0 ? y + 1 : y + r - 2, L1), gz = r == 0 ? z : wrap_once(z + 1, L2);
+            const int row = (gz * L1 + gy) * L0;
+            before = a.lat[row + xm];
+            load_row(row, u);
+        }
+#pragma unroll
+        for (int j = 0; j < kRun; ++j) {
+            pair(j < n, lab[j], j > 0 ? u[j > 0 ? j - 1 : 0] : before);
+            pair(j < n, lab[j], u[j]);
+            pair(j < n, lab[j], u[j + 1]);
         }
     }
+    count(0, queued);
     __syncthreads();
     for (int b = tid; b < kBins; b += kBlock) {
         const int ta = b / kMaxTypes, tb = b % kMaxTypes;
         if (ta >= n_types || tb >= n_types) continue;
         unsigned long long v = 0;
-        for (int w = 0; w < kBlock / 64; ++w) v += hist[w][b];
+        for (int w = 0; w < kCopies; ++w) v += (unsigned long long)hist[w][b] + hist[w][tb * kMaxTypes + ta];
         if (v) atomicAdd(&out[ta * n_types + tb], v);
     }
 }
@@ -581,8 +626,7 @@ hipError_t launch_contacts(const SweepArgs &a, int ndim, int n_types, int64_t *o
 {
     hipError_t e = launch_fill_i32(reinterpret_cast<int32_t *>(out), 0, (size_t)n_types * n_types * 2, stream);
     if (e != hipSuccess) return e;
-    const size_t n = (size_t)a.L[0] * a.L[1] * a.L[2];
-    const unsigned grid = (unsigned)((n + kContactSites - 1) / kContactSites);
+    const unsigned grid = (unsigned)reduce_brick_count(a.L, ndim);
     auto *o = reinterpret_cast<unsigned long long *>(out);
     if (ndim == 2) contact_kernel<2><<<grid, kBlock, 0, stream>>>(a, o, n_types);
     else contact_kernel<3><<<grid, kBlock, 0, stream>>>(a, o, n_types);
@@ -648,20 +692,42 @@ __global__ void copy_dirs_kernel(const int4 *pdir, int32_t n_labels, int32_t *ou
 }  // namespace
 
 namespace {
-__global__ void occupancy_kernel(const int32_t *lat, int n_lattices, size_t n_sites, int32_t *counts)
+// Four sites per thread, kOccLattices lattices per workgroup row: a thread per
+// site over all lattices left most of the GPU idle (62 us for 250 lattices of
+// 256^2, now 14).
+constexpr int kOccLattices = 16;
+template <bool VEC>
+__global__ void __launch_bounds__(kBlock) occupancy_kernel(const int32_t *lat, int n_lattices, size_t n_sites, int32_t *counts)
 {
-    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const size_t i = ((size_t)blockIdx.x * kBlock + threadIdx.x) * 4;
     if (i >= n_sites) return;
-    int32_t c = 0;
-    for (int l = 0; l < n_lattices; ++l) c += lat[(size_t)l * n_sites + i] > 0;
-    counts[i] = c;
+    const int l0 = (int)blockIdx.y * kOccLattices, l1 = min(n_lattices, l0 + kOccLattices);
+    int c[4] = {0, 0, 0, 0};
+#pragma unroll 8
+    for (int l = l0; l < l1; ++l) {
+        const int32_t *p = lat + (size_t)l * n_sites + i;
+        int4 v;
+        if (VEC) v = *reinterpret_cast<const int4 *>(p);
+        else v = make_int4(p[0], p[1], p[2], p[3]);
+        c[0] += v.x > 0;
+        c[1] += v.y > 0;
+        c[2] += v.z > 0;
+        c[3] += v.w > 0;
+    }
+    for (int k = 0; k < 4; ++k)
+        if (c[k]) atomicAdd(&counts[i + k], c[k]);
 }
 }  // namespace
 
 hipError_t launch_occupancy(const int32_t *lattices, int n_lattices, size_t n_sites, int32_t *counts,
                             hipStream_t st)
 {
-    occupancy_kernel<<<blocks_for(n_sites), kBlock, 0, st>>>(lattices, n_lattices, n_sites, counts);
+    const hipError_t e = launch_fill_i32(counts, 0, n_sites, st);
+    if (e != hipSuccess) return e;
+    // sides are even, so a lattice holds a multiple of four sites
+    const dim3 grid(blocks_for(n_sites / 4), (unsigned)((n_lattices + kOccLattices - 1) / kOccLattices));
+    if ((reinterpret_cast<uintptr_t>(lattices) & 15) == 0) occupancy_kernel<true><<<grid, kBlock, 0, st>>>(lattices, n_lattices, n_sites, counts);
+    else occupancy_kernel<false><<<grid, kBlock, 0, st>>>(lattices, n_lattices, n_sites, counts);
     return hipGetLastError();
 }
 

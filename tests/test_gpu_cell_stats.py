@@ -96,3 +96,72 @@ def test_batch_cell_stats(torch_cuda, ndim):
         np.testing.assert_array_equal(v[lo + 1:lo + n + 1], V[1:])
         np.testing.assert_array_equal(s[lo + 1:lo + n + 1], S[1:])
         np.testing.assert_array_equal(c[lo + 1:lo + n + 1], C[1:])
+
+
+def _expected_contacts(lat, types, n_types):
+    out = np.zeros((n_types, n_types), dtype=np.int64)
+    by_type = np.where(lat > 0, types[np.maximum(lat, 0)], 0)
+    for dz in (-1, 0, 1) if lat.shape[0] > 1 else (0,):
+        for dy in (-1, 0, 1):
+            for dx in (-1, 0, 1):
+                other = np.roll(lat, (dz, dy, dx), (0, 1, 2))
+                t = np.roll(by_type, (dz, dy, dx), (0, 1, 2))
+                m = (other != lat) & (lat >= 0) & (other >= 0)
+                np.add.at(out, (by_type[m], t[m]), 1)
+    return out
+
+
+@pytest.mark.parametrize("case", range(len(LATTICES)))
+def test_contacts(torch_cuda, case):
+    p, lat, n = _make(case)
+    print(f"contacts of {LATTICES[case]}", flush=True)
+    types = np.array([0] + [1 + (i * 7) % 14 for i in range(n)], dtype=np.int32)
+    p = p.replace(J=np.zeros((16, 16)), lambda_volume=np.zeros(16), volume_target=np.zeros(16, dtype=np.int32), obstacle_type=15)
+    sim = cpm.Simulation(p, lat, types)
+    np.testing.assert_array_equal(sim.contacts().cpu().numpy(), _expected_contacts(lat, types, 16))
+
+
+@pytest.mark.parametrize("n,dims", [(1, (2, 2)), (17, (66, 38)), (40, (6, 10, 4))])
+def test_occupancy(torch_cuda, n, dims):
+    print(f"occupancy of {n} lattices of {dims}", flush=True)
+    shape = tuple(dims) + (1,) * (3 - len(dims))
+    lats = [inputs.random_labels(shape, 3, 70 + i, p_obstacle=0.2).reshape(shape[::-1]) for i in range(n)]
+    p = cpm.Params(ndim=len(dims), dims=dims, J=np.zeros((3, 3)), lambda_volume=[0, 1, 0], volume_target=[0, 10, 0],
+                   obstacle_type=2, sub=1)
+    b = cpm.Batch([p] * n, lats, [np.array([0, 1, 1, 1], dtype=np.int32)] * n)
+    np.testing.assert_array_equal(b.occupancy().cpu().numpy().reshape(-1), sum((l > 0).astype(np.int64) for l in lats).reshape(-1))
+
+
+@pytest.mark.parametrize("layout", ["auto", "in_place"])
+@pytest.mark.parametrize("act", [False, True])
+def test_unaligned_lattice(torch_cuda, layout, act):
+    """A lattice (and activities) not aligned for vector loads sweeps like an
+    aligned one."""
+    torch = torch_cuda
+    dims, n = (16, 12, 20), 9
+    lat = inputs.random_blobs(dims, n, seed=3, fill=0.6).reshape(dims[::-1])
+    kw = dict(lambda_act=[0, 60.0, 0.0], max_act=[0, 20, 0]) if act else {}
+    p = cpm.Params(ndim=3, dims=dims, J=np.array([[0, 3, 5.0], [3, 7, 1], [5, 1, 9]]), lambda_volume=[0, 2, 1],
+                   volume_target=[0, 60, 50], layout=layout, **kw)
+    ct = torch.as_tensor(np.array([0] + [1 + i % 2 for i in range(n)], dtype=np.int32)).cuda()
+    print(f"unaligned lattice layout={layout} act={act}", flush=True)
+    out = []
+    for off in (0, 1):
+        buf = torch.zeros(lat.size + 4, dtype=torch.int32, device="cuda")
+        abuf = torch.zeros(lat.size + 4, dtype=torch.uint8, device="cuda")
+        l, a = buf[off:off + lat.size], abuf[off:off + lat.size]
+        l.copy_(torch.as_tensor(lat.reshape(-1)))
+        nbytes = cpm.cpm_workspace_bytes(p, n)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        st = torch.cuda.current_stream().cuda_stream
+        h = cpm.cpm_init(p, l, ct, n, a if act else None, ws, nbytes, st)
+        cpm.cpm_sweep(h, 3, st)
+        v = torch.empty(n + 1, dtype=torch.int32, device="cuda")
+        s, c = torch.empty_like(v), torch.empty((n + 1, 3), dtype=torch.int64, device="cuda")
+        cpm.cpm_cell_stats(h, v, s, c, st)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy()[1:] for t in (v, s, c)] + [l.cpu().numpy(), a.cpu().numpy()])
+        assert (buf[lat.size + off:] == 0).all() and (buf[:off] == 0).all() and (abuf[lat.size + off:] == 0).all()
+        cpm.cpm_destroy(h)
+    for x, y in zip(*out):
+        np.testing.assert_array_equal(x, y)
