@@ -999,10 +999,10 @@ int sweep_impl(cpm_handle *h, int32_t n_mcs, hipStream_t st)
             if (e != hipSuccess) return device_fail(e, "activation");
             ++h->activation;
         }
-        if (h->act)
-            e = h->words == cpm::kWordsPackedAct ? cpm::launch_act_decay_words(h->args.lat, n_sites, st)
-                                                 : cpm::launch_act_decay(h->args.act, n_sites, st);
-        if (h->act && e != hipSuccess) return device_fail(e, "act decay");
+        // (the last decay of packed words comes with their unpacking)
+        if (h->act && h->words != cpm::kWordsPackedAct) e = cpm::launch_act_decay(h->args.act, n_sites, st);
+        else if (h->act && i + 1 < n_mcs) e = cpm::launch_act_decay_words(h->args.lat, n_sites, st);
+        if (e != hipSuccess) return device_fail(e, "act decay");
         if (h->pdir && (e = persist_step(h, ++h->persist_t, h->words, st)) != hipSuccess)
             return device_fail(e, "persistence update");
         ++h->mcs;

@@ -326,6 +326,7 @@ hipError_t launch_unpack(int32_t *lat, size_t n, hipStream_t stream);
 // The same with the activity in bits 24..31 (label + 1 in 0..19, type in 20..23).
 hipError_t launch_pack_act(int32_t *lat, const uint8_t *act, const int32_t *cell_type, int obstacle_type, size_t n,
                            hipStream_t stream);
+// Back, with the Act decay of the last MCS.
 hipError_t launch_unpack_act(int32_t *lat, uint8_t *act, size_t n, hipStream_t stream);
 hipError_t launch_act_decay_words(int32_t *lat, size_t n, hipStream_t stream);
 // Every lattice of a batch to (to_words) or from label-type-activity words.
