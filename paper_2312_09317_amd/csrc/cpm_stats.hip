@@ -93,9 +93,11 @@ __device__ __forceinline__ void write_moments(const double *r, double *o)
 {
     auto moments = [](double n, double s1, double s2, double *mv) {
         if (n > 0) {
-            const double mean = s1 / n;
-            mv[0] = mean;
-            mv[1] = s2 / n - mean * mean;
+            // variance (n s2 - s1^2) / n^2, both products with their rounding
+            // errors: s2 / n - mean^2 lost the digits that cancel
+            const double p = s1 * s1, pe = fma(s1, s1, -p), q = n * s2, qe = fma(n, s2, -q);
+            mv[0] = s1 / n;
+            mv[1] = ((q - p) + (qe - pe)) / (n * n);
         } else {
             mv[0] = 0.0;
             mv[1] = 0.0;
