@@ -327,13 +327,15 @@ bool tile_geometry(const cpm_params *p, bool mirror, int force_layout, cpm::Tile
 // Resident sweeps: how a lattice is cut so that a part's box (`cell` bytes a
 // site), the threshold tables and, for an uncut lattice, the counters fit
 // `budget` bytes of LDS: uncut if that fits, else into the fewest parts, of
-// those the ones with the smallest box.  False when more than max_parts are
-// needed.
+// those the ones with the smallest box; a part has at most max_areas.  False
+// when more than max_parts are needed.
 constexpr int kResidentMaxAreas = 32 * 512;  // a thread keeps a bit per attempt of an activation
 constexpr uint32_t kResidentSpinLimit = 1u << 24;
 constexpr int kResidentBatchParts = 16;      // most parts of a batch's lattice
+constexpr size_t kResidentCUs = 256;         // of the MI355X: one resident workgroup each
+constexpr int kResidentFine = 1700;          // areas per part below which finer cuts no longer pay
 constexpr size_t kResidentBudget = kLdsLimit - cpm::kResidentStaticLds;
-bool resident_split(const cpm_params *p, size_t cell, int32_t n_labels, int32_t n_ti, size_t budget, int max_parts,
+bool resident_split(const cpm_params *p, size_t cell, int32_t n_labels, int32_t n_ti, size_t budget, int max_parts, int max_areas,
                     cpm::ResidentSplit &sp, size_t &lds, int &areas)
 {
     const int s = p->sub, R = p->act_enabled ? 2 : 1;
@@ -360,7 +362,7 @@ bool resident_split(const cpm_params *p, size_t cell, int32_t n_labels, int32_t 
     if (cap >= all / 8 || p->ndim == 3) lds += lists(cap);
     else lds = budget + 1;
     if (s > 15) return false;  // the kernel divides draws by s in 16 bits
-    if (lds <= budget && (int64_t)na0 * na1 * na2 <= kResidentMaxAreas) {
+    if (lds <= budget && (int64_t)na0 * na1 * na2 <= max_areas) {
         sp = cpm::ResidentSplit{{na1, na2}, {1, 1}, (int32_t)cap};
         areas = na0 * na1 * na2;
         return true;
@@ -375,7 +377,7 @@ bool resident_split(const cpm_params *p, size_t cell, int32_t n_labels, int32_t 
             const size_t b2 = p->ndim == 3 ? 2 * (size_t)s * T2 + (n2 > 1 ? R : 0) : 1;
             const int64_t ar = (int64_t)na0 * T1 * T2;
             const size_t bytes = up16((size_t)p->dims[0] * b1 * b2 * cell) + tables + heads(ar) + bits(ar) + lists(p->ndim == 2 ? (ar + 1) / 2 : 0);
-            if (bytes > budget || ar > kResidentMaxAreas) continue;
+            if (bytes > budget || ar > max_areas) continue;
             if (best && (n1 * n2 > best || (n1 * n2 == best && bytes >= lds))) continue;
             best = n1 * n2;
             lds = bytes;
@@ -918,7 +920,7 @@ int init_impl(const cpm_params *params, int32_t *d_lattice, const int32_t *d_cel
         int areas = 0;
         cpm::ResidentSplit sp{};
         h->resident = resident_split(params, h->words == cpm::kWords16 ? 2 : 4, n_cells + 1, h->host_model->n_ti,
-                                     kResidentBudget, 1, sp, h->resident_lds, areas) &&
+                                     kResidentBudget, 1, kResidentMaxAreas, sp, h->resident_lds, areas) &&
                       areas <= resident_areas(params);
         h->whole = cpm::ResidentPart{0, 1, 0, sp.T[0], 0, sp.T[1], n_cells + 1, sp.hot_cap};
         h->resident_threads = resident_threads(areas);
@@ -1450,8 +1452,8 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
     // lattice can be cut into few parts.  A few large lattices, though, leave
     // most of the GPU idle that way, and sweep faster by a launch per
     // activation over all of it (us for one sample and 4 MCS, resident :
-    // launches): 8 of 256^2 644 : 604, 32 of 256^2 644 : 758; 8 of 64..512 per
-    // side 696 : 647, 16 713 : 714, 32 762 : 822, 512 of 160..512 5,134 : 6,561.
+    // launches, uncut): 8 of 256^2 644 : 604, 32 of 256^2 644 : 758; 8 of 64..512
+    // per side 696 : 647, 16 713 : 714, 32 762 : 822, 512 of 160..512 5,134 : 6,561.
     b->resident = (b->act16 || b->act_words || b->mirror) && !(b->ndim == 3 && b->k > 1);
     for (int32_t i = 0; i < n && b->resident; ++i) b->resident = library_tiling(&params[i]);
     if (b->resident) {
@@ -1459,15 +1461,35 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
         struct Cut { cpm::ResidentSplit sp; int32_t i; int areas; };
         std::vector<Cut> cuts;
         int max_areas = 1;
-        for (int32_t i = 0; i < n && b->resident; ++i) {
-            Cut c{};
-            size_t bytes = 0;
-            c.i = i;
-            b->resident = resident_split(&params[i], cell, n_cells[i] + 1, b->models[i]->n_ti,
-                                         kResidentBudget, kResidentBatchParts, c.sp, bytes, c.areas);
-            b->resident_lds = std::max(b->resident_lds, bytes);
-            max_areas = std::max(max_areas, c.areas);
-            cuts.push_back(c);
+        // Act batches whose lattices do not fill the GPU are cut finer, as
+        // long as every part has a CU of its own: their cells disperse, and a
+        // part's time goes with its areas (us for two samples and 6 MCS after
+        // 180 MCS, by launches : uncut : parts of up to 2,048 : 1,024 areas):
+        // 100 of 100..256 per side 1,361 : 1,593 : 898 : 842, 64 of 64..512
+        // 1,644 : 1,551 : 969 : 952, 16 of 256^2 967 : 931 : 946 : 787, but
+        // 128 of 160^2 (1,600 areas each) 1,357 : 701 : 713 : 818
+        for (int limit = kResidentMaxAreas; b->resident; limit = limit > 4096 ? 4096 : limit / 2) {
+            std::vector<Cut> finer;
+            size_t lds_max = 0, parts = 0;
+            int most = 1;
+            bool fits = true;
+            for (int32_t i = 0; i < n && fits; ++i) {
+                Cut c{};
+                size_t bytes = 0;
+                c.i = i;
+                fits = resident_split(&params[i], cell, n_cells[i] + 1, b->models[i]->n_ti, kResidentBudget,
+                                      kResidentBatchParts, limit, c.sp, bytes, c.areas);
+                lds_max = std::max(lds_max, bytes);
+                most = std::max(most, c.areas);
+                parts += (size_t)(c.sp.parts[0] * c.sp.parts[1]);
+                finer.push_back(c);
+            }
+            if (limit == kResidentMaxAreas) b->resident = fits;
+            else if (!fits || parts > kResidentCUs) break;
+            cuts.swap(finer);
+            b->resident_lds = lds_max;
+            max_areas = most;
+            if (!b->act || most <= kResidentFine) break;
         }
         b->resident_threads = resident_threads(max_areas);
         bool cut = false;
