@@ -41,6 +41,8 @@ namespace {
 
 // MCS between two searches for hot areas.
 constexpr int kFindHot = 4;
+// An entry of a list of hot areas that has not been written yet.
+constexpr uint16_t kNoArea = 0xFFFF;
 
 // LDS of a workgroup beside its box, its counters and the tables sized by the
 // host (resident_tables).
@@ -71,6 +73,18 @@ template <typename T>
 __device__ __forceinline__ void agent_store(T *p, T v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A word of LDS that other waves may be writing.
+template <typename T>
+__device__ __forceinline__ T lds_load(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ void lds_store(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // The word of a site as the sweep stores it.
@@ -418,6 +432,11 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     // is not drawn.  `mark` adds the sub-areas that see site (x, y), whose
     // label has just changed; `find_hot` lists all anew.  A list that has
     // grown past its room stands for all areas.  Uncut lattices only.
+    //
+    // `mark` counts an entry before it writes it, and other waves draw ahead
+    // meanwhile: every entry past the count of `find_hot` holds kNoArea until
+    // it is written, and a thread that reads kNoArea makes no draw from it.
+    // After the barrier of the step all counted entries are written.
     auto mark = [&](int x, int y) {
         const int gx[3] = {(int)by_s32.div((uint32_t)wrap_min(x - 1, L0)), (int)by_s32.div((uint32_t)wrap_min(x + 1, L0)), x};
         const int gy[3] = {(int)by_s32.div((uint32_t)wrap_min(y - 1, L1)), (int)by_s32.div((uint32_t)wrap_min(y + 1, L1)), y};
@@ -426,11 +445,11 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
             const uint32_t bit = 1u << (area & 31);
             if (!(old & bit) && !(atomicOr(hot_bits + c * hot_words + (area >> 5), bit) & bit)) {
                 const int slot = atomicAdd(&sh.hot_n[c], 1);
-                if (slot < hot_cap) hot[c * hot_cap + slot] = (uint16_t)area;
+                if (slot < hot_cap) lds_store(&hot[c * hot_cap + slot], (uint16_t)area);
             }
         };
         auto word = [&](int i, int j) {
-            return hot_bits[((gx[i] & 1) | ((gy[j] & 1) << 1)) * hot_words + (((gx[i] >> 1) + na0 * (gy[j] >> 1)) >> 5)];
+            return lds_load(&hot_bits[((gx[i] & 1) | ((gy[j] & 1) << 1)) * hot_words + (((gx[i] >> 1) + na0 * (gy[j] >> 1)) >> 5)]);
         };
         // s >= 2: of x - 1, x, x + 1 the outer two lie in every sub-area that sees x
         const uint32_t w0 = word(0, 0), w1 = word(1, 0), w2 = word(0, 1), w3 = word(1, 1);
@@ -472,6 +491,9 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
                 if (is && slot < hot_cap) hot[c * hot_cap + slot] = (uint16_t)area;
             }
         }
+        __syncthreads();
+        for (int i = tid; i < 4 * hot_cap; i += block)
+            if (i % hot_cap >= sh.hot_n[i / hot_cap]) hot[i] = kNoArea;
         __syncthreads();
     };
 
@@ -667,7 +689,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     auto step_of = [&](int seq, uint32_t alpha) {
         Step st{areas, seq * 4, false, false};
         if (HOT) {
-            const int n = sh.hot_n[alpha & 3];
+            const int n = lds_load(&sh.hot_n[alpha & 3]);
             st.listed = n <= hot_cap;
             if (st.listed) st.n = n;
             st.few = st.listed && n <= half;
@@ -676,10 +698,11 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
         return st;
     };
     auto area_number = [&](uint32_t alpha, bool listed, int i) {
-        return HOT && listed ? (int)hot[__umul24(alpha & 3u, (uint32_t)hot_cap) + (uint32_t)i] : i;
+        return HOT && listed ? (int)lds_load(&hot[__umul24(alpha & 3u, (uint32_t)hot_cap) + (uint32_t)i]) : i;
     };
     // This thread's first attempts of the next step, drawn ahead; they stand
-    // if the step is then taken as its tag says (the lists only grow).
+    // if the step is then taken as its tag says: entries below ahead_n had
+    // been written when they were drawn from, and stay until the next search.
     Draw ahead[kGroup];
     int ahead_tag = -1, ahead_n = 0;
     auto draw_ahead = [&](int seq, uint32_t mcs, uint32_t alpha, int j) {
@@ -688,13 +711,20 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
         ahead_n = st.n;
         if (st.few) {
             const int i = tid - (seq & 1) * half;
-            if (i >= 0 && i < st.n) ahead[0] = draw(area_of(area_number(alpha, true, i)), mcs, alpha, j);
+            if (i >= 0 && i < st.n) {
+                const int area = area_number(alpha, true, i);
+                if (area == kNoArea) ahead_n = i;
+                else ahead[0] = draw(area_of(area), mcs, alpha, j);
+            }
             return;
         }
 #pragma unroll
         for (int r = 0; r < kGroup; ++r) {
             const int i = tid + r * block;
-            if (i < st.n) ahead[r] = draw(area_of(area_number(alpha, st.listed, i)), mcs, alpha, j);
+            if (i >= st.n) continue;
+            const int area = area_number(alpha, st.listed, i);
+            if (HOT && area == kNoArea) ahead_n = min(ahead_n, i);
+            else ahead[r] = draw(area_of(area), mcs, alpha, j);
         }
     };
     __syncthreads();

@@ -152,3 +152,19 @@ def test_batch_with_cut_lattices(torch_cuda, case):
         lats.append(lat)
         cts.append(np.array([0] + [1 + (j % types) for j in range(m)], dtype=np.int32))
     _batches_same(torch_cuda, params, lats, cts, "in_place" if k == 1 else "box", 5, mode_between="eager" if case % 2 == 0 else None)
+
+
+@pytest.mark.parametrize("s,k", [(1, 1), (2, 1), (2, 4), (4, 2)])
+def test_hot_lists_grow_while_drawn_ahead(torch_cuda, s, k):
+    # many small lattices of a few fast cells: areas turn hot in every step,
+    # while the other half of the workgroup draws the next one's attempts from
+    # the same lists
+    print(f"growing hot lists s={s} k={k}", flush=True)
+    params, lats, cts = [], [], []
+    for i in range(192):
+        d = (64 + 16 * (i % 3), 48 + 16 * (i % 2))
+        lat, m = _lattice("blobs", d, 4, 400 + i, False)
+        params.append(_params(d, 1, 25.0 + i % 7, sub=s, attempts=k, lattice_id=i))
+        lats.append(lat)
+        cts.append(np.array([0] + [1] * m, dtype=np.int32))
+    _batches_same(torch_cuda, params, lats, cts, "in_place" if k == 1 else "box", 14)
