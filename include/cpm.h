@@ -327,15 +327,21 @@ int cpm_batch_use_graph(cpm_batch *b, int32_t enabled);
  * whole grid synchronises between activations).  Mode 2 needs batches swept
  * in place (k = 1; CPM_ENOTSUP otherwise).  A barrier wait is bounded (see
  * cpm_batch_set_barrier_spin_limit): a launch whose wait runs out ends
- * early and leaves the batch invalid (so does, after a fixed limit of about ten
- * seconds, a default launch whose parts of one lattice wait for each other),
- * which cpm_batch_attempt_stats and
- * cpm_batch_check_invariants report as CPM_EDEVICE. */
+ * early and leaves the batch invalid, which cpm_batch_attempt_stats and
+ * cpm_batch_check_invariants report as CPM_EDEVICE.  (In mode 0 the parts of
+ * a lattice come together before they change it: where other streams keep
+ * the CUs busy for longer than the limit, the lattice is swept by one
+ * workgroup instead, with the same results.) */
 int cpm_batch_launch_mode(cpm_batch *b, int32_t mode);
 /* Polls of one barrier wait before a persistent launch gives up (default
- * 2^20, about a second; a barrier normally completes in microseconds).
- * Pure host. */
+ * 2^20, about a second; a barrier normally completes in microseconds), and of
+ * the wait for the parts of a lattice to come together in mode 0 (default
+ * 2^21).  Pure host. */
 int cpm_batch_set_barrier_spin_limit(cpm_batch *b, uint32_t polls);
+/* Lattices that sweeps of this batch took on one workgroup because their
+ * parts did not come together, since init, one per launch; waits for the
+ * stream. */
+int cpm_batch_alone_count(cpm_batch *b, uint64_t *count, void *stream);
 /* Runs n_mcs MCS of the serial CPM on every lattice (Methods, first
  * paragraph; the reference of Fig. 5 and Fig. 6E): per MCS, N = sites copy
  * attempts, attempt i at target floor(u0 * N / 2^32) with the Philox counter

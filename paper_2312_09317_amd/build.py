@@ -14,7 +14,7 @@ SOURCES = ["cpm_sweep.hip", "cpm_sweep_inst.hip", "cpm_resident.hip", "cpm_seria
            "emu_kernels.hip", "cpm_api.cpp", "emu_api.cpp"]
 # the activation kernels are instantiated in groups, one compilation each
 SWEEP_PARTS = 7
-RESIDENT_PARTS = 5
+RESIDENT_PARTS = 6
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     # keep the compiler from emitting packed FP32 instructions

@@ -67,7 +67,7 @@ CENTROID_MODES = {"recount": 0, "incremental": 1}
 EXPORTS = ("cpm_validate", "cpm_workspace_bytes", "cpm_tile_shape", "cpm_init", "cpm_init_static", "cpm_sweep", "cpm_cell_stats", "cpm_contacts",
            "cpm_persistence", "cpm_counters", "cpm_check_invariants", "cpm_attempt_stats", "cpm_set_mcs", "cpm_get_mcs", "cpm_destroy",
            "cpm_batch_workspace_bytes", "cpm_batch_init", "cpm_batch_sweep", "cpm_batch_sweep_serial", "cpm_batch_occupancy", "cpm_batch_use_graph", "cpm_batch_launch_mode",
-           "cpm_batch_set_barrier_spin_limit", "cpm_batch_counters",
+           "cpm_batch_set_barrier_spin_limit", "cpm_batch_alone_count", "cpm_batch_counters",
            "cpm_batch_cell_stats", "cpm_batch_attempt_stats", "cpm_batch_check_invariants", "cpm_batch_sample", "cpm_batch_summary", "cpm_batch_autocorrelation",
            "cpm_batch_set_mcs", "cpm_batch_get_mcs",
            "cpm_batch_destroy", "cpm_strerror", "cpm_last_error")
@@ -111,6 +111,7 @@ def load(path: str = LIB_PATH):
     l.cpm_batch_use_graph.argtypes = [P, I32]
     l.cpm_batch_launch_mode.argtypes = [P, I32]
     l.cpm_batch_set_barrier_spin_limit.argtypes = [P, ctypes.c_uint32]
+    l.cpm_batch_alone_count.argtypes = [P, ctypes.POINTER(ctypes.c_uint64), P]
     l.cpm_batch_sweep_serial.argtypes = [P, I32, P]
     l.cpm_batch_occupancy.argtypes = [P, P, P]
     l.cpm_batch_counters.argtypes = [P, P, P, P]
@@ -472,6 +473,12 @@ def cpm_batch_launch_mode(h: int, mode) -> None:
 
 def cpm_batch_set_barrier_spin_limit(h: int, polls: int) -> None:
     _check(load().cpm_batch_set_barrier_spin_limit(h, polls), "cpm_batch_set_barrier_spin_limit")
+
+
+def cpm_batch_alone_count(h: int, stream: int) -> int:
+    v = ctypes.c_uint64(0)
+    _check(load().cpm_batch_alone_count(h, ctypes.byref(v), stream), "cpm_batch_alone_count")
+    return v.value
 
 
 def cpm_batch_use_graph(h: int, enabled: bool) -> None:

@@ -52,6 +52,13 @@ struct cpm_handle {
     int static_device = -1;          // device whose static workspace the handle holds (cpm_init_static), else -1
 };
 
+// Polls (of about a microsecond) in a launch whose workgroups meet: at a
+// meeting, where all of them run, a limit no launch reaches; before the first
+// one, how long parts of a lattice wait for the others to find a CU before
+// one workgroup sweeps the lattice alone.
+constexpr uint32_t kResidentSpinLimit = 1u << 24;
+constexpr uint32_t kResidentGatherLimit = 1u << 21;
+
 struct cpm_batch {
     int32_t n = 0;
     int32_t ndim = 0, s = 0, k = 0;
@@ -98,8 +105,8 @@ struct cpm_batch {
     uint32_t *arrivals = nullptr;
     size_t resident_lds = 0;
     int resident_threads = 0;
-    bool parts_meet = false;         // some lattice has several parts
-    uint32_t meetings = 0, tickets = 0;
+    int most_parts = 1;              // of one lattice
+    uint32_t gather_limit = kResidentGatherLimit;
     bool lists_pending = false;      // a launch per activation left accepted copies to re-add
     hipGraphExec_t mcs_graph = nullptr;  // one MCS: every activation, act decay, MCS counter
     ~cpm_batch()
@@ -330,7 +337,6 @@ bool tile_geometry(const cpm_params *p, bool mirror, int force_layout, cpm::Tile
 // those the ones with the smallest box; a part has at most max_areas.  False
 // when more than max_parts are needed.
 constexpr int kResidentMaxAreas = 32 * 512;  // a thread keeps a bit per attempt of an activation
-constexpr uint32_t kResidentSpinLimit = 1u << 24;
 constexpr int kResidentBatchParts = 16;      // most parts of a batch's lattice
 constexpr size_t kResidentCUs = 256;         // of the MI355X: one resident workgroup each
 constexpr int kResidentFine = 1700;          // areas per part below which finer cuts no longer pay
@@ -933,12 +939,6 @@ int init_impl(const cpm_params *params, int32_t *d_lattice, const int32_t *d_cel
 
 namespace {
 
-// Meetings of a lattice's parts in a resident launch.
-uint32_t resident_meetings(int32_t n_mcs, uint32_t n_act, bool act)
-{
-    return 1u + (uint32_t)n_mcs * n_act + (act ? (uint32_t)n_mcs - 1u : 0u);
-}
-
 // MCS per resident launch: as many as keep a launch to a fraction of a second.
 int32_t resident_chunk(uint32_t n_act) { return (int32_t)std::max<uint32_t>(1u, 65536u / n_act); }
 
@@ -960,8 +960,7 @@ int sweep_resident_impl(cpm_handle *h, int32_t n_mcs, uint32_t n_act, hipStream_
     c.ext = h->args.pdir || h->args.chem;
     for (int32_t done = 0; done < n_mcs;) {
         const int32_t n = std::min(chunk, n_mcs - done);
-        c.launch = cpm::ResidentLaunch{nullptr, nullptr, nullptr, 0, 0, (uint32_t)h->mcs, n, n_act, 0,
-                                       (int32_t)(h->activation & 1)};
+        c.launch = cpm::ResidentLaunch{nullptr, nullptr, false, (uint32_t)h->mcs, n, n_act, 0, 0, (int32_t)(h->activation & 1)};
         const bool d2 = h->ndim == 2;
         hipError_t e = h->act ? (d2 ? cpm::launch_resident_act32_2d(c, st) : cpm::launch_resident_act32_3d(c, st))
                               : (d2 ? cpm::launch_resident_u16_2d(c, st) : cpm::launch_resident_u16_3d(c, st));
@@ -1504,7 +1503,7 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
             for (const Cut &c : cuts) {
                 const SweepArgs &a = b->args[c.i];
                 const int q = c.sp.parts[0] * c.sp.parts[1];
-                b->parts_meet = b->parts_meet || q > 1;
+                b->most_parts = std::max(b->most_parts, q);
                 for (int j = 0; j < q; ++j) {
                     cpm::ResidentPart pt{};
                     pt.lattice = c.i;
@@ -1597,6 +1596,26 @@ hipError_t capture_mcs(cpm_batch *b, uint32_t n_act)
 
 namespace {
 
+// CUs that kernels of a stream may run on (all of them if it cannot be told).
+int stream_cus(hipStream_t st)
+{
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return INT32_MAX;
+    }
+    int n = 0;
+    for (uint32_t m : mask) n += __builtin_popcount(m);
+    return n ? n : INT32_MAX;
+}
+
+// Whether a sweep on this stream keeps the lattices in LDS: the parts of a
+// lattice that meet need a CU each.
+bool resident_on(const cpm_batch *b, hipStream_t st)
+{
+    return b->resident && b->mode == 0 && (b->most_parts == 1 || stream_cus(st) >= b->most_parts);
+}
+
 // n_mcs MCS of a batch whose lattices stay in LDS.
 int batch_sweep_resident(cpm_batch *b, int32_t n_mcs, uint32_t n_act, hipStream_t st)
 {
@@ -1618,16 +1637,15 @@ int batch_sweep_resident(cpm_batch *b, int32_t n_mcs, uint32_t n_act, hipStream_
     c.ext = b->launch.ext;
     for (int32_t done = 0; done < n_mcs;) {
         const int32_t n = std::min(resident_chunk(n_act), n_mcs - done);
-        c.launch = cpm::ResidentLaunch{b->bar, b->arrivals, b->parts_meet ? &b->bar->ticket : nullptr, b->tickets,
-                                       b->meetings, (uint32_t)b->mcs, n, n_act, kResidentSpinLimit,
-                                       (int32_t)(b->activation & 1)};
+        c.launch = cpm::ResidentLaunch{b->bar, b->arrivals, b->most_parts > 1, (uint32_t)b->mcs, n, n_act,
+                                       b->gather_limit, kResidentSpinLimit, (int32_t)(b->activation & 1)};
         const bool d2 = b->ndim == 2;
         e = b->act16       ? cpm::launch_resident_act16(c, st)
             : b->act_words ? (d2 ? cpm::launch_resident_act32_2d(c, st) : cpm::launch_resident_act32_3d(c, st))
                            : (d2 ? cpm::launch_resident_u16_2d(c, st) : cpm::launch_resident_u16_3d(c, st));
+        if (e == hipSuccess && b->most_parts > 1)
+            e = cpm::launch_resident_alone(b->d_args, b->stats_tables.label_off, b->n, b->ndim, b->act, c.launch, st);
         if (e != hipSuccess) return device_fail(e, "resident sweep");
-        if (b->parts_meet) b->tickets += (uint32_t)c.grid;
-        b->meetings += resident_meetings(n, n_act, b->act);
         b->activation += (uint64_t)n_act * (uint64_t)n;
         b->mcs += (uint64_t)n;
         b->mcs_run += (uint64_t)n;
@@ -1650,7 +1668,7 @@ int cpm_batch_sweep(cpm_batch *b, int32_t n_mcs, void *stream)
     for (int d = 0; d < b->ndim; ++d) sd *= b->s;
     const uint32_t n_act = (uint32_t)(((int64_t)1 << b->ndim) * sd / b->k);
     hipError_t e;
-    if (b->resident && b->mode == 0) return batch_sweep_resident(b, n_mcs, n_act, st);
+    if (resident_on(b, st)) return batch_sweep_resident(b, n_mcs, n_act, st);
     b->lists_pending = true;
     if (b->mode == 0 && !b->mcs_graph && (e = capture_mcs(b, n_act)) != hipSuccess)
         return device_fail(e, "capture MCS graph");
@@ -1751,7 +1769,18 @@ int cpm_batch_launch_mode(cpm_batch *b, int32_t mode)
 int cpm_batch_set_barrier_spin_limit(cpm_batch *b, uint32_t polls)
 {
     if (!b) return fail(CPM_EINVAL, "batch is NULL");
-    b->spin_limit = polls;
+    b->spin_limit = b->gather_limit = polls;
+    return CPM_OK;
+}
+
+int cpm_batch_alone_count(cpm_batch *b, uint64_t *count, void *stream)
+{
+    if (!b || !count) return fail(CPM_EINVAL, "NULL argument");
+    cpm::GridBarrier g{};
+    hipError_t e = hipMemcpyAsync(&g, b->bar, sizeof(g), hipMemcpyDeviceToHost, as_stream(stream));
+    if (e == hipSuccess) e = hipStreamSynchronize(as_stream(stream));
+    if (e != hipSuccess) return device_fail(e, "read barrier");
+    *count = g.alone;
     return CPM_OK;
 }
 

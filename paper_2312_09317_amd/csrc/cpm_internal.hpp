@@ -178,7 +178,10 @@ struct GridBarrier {
     uint32_t gen;
     uint32_t abort;
     uint32_t act_overflow;  // sticky: an activity too large for 16-bit words was met
-    uint32_t ticket;        // parts taken by resident launches since init (only grows)
+    // resident launches whose parts meet: parts taken by the launch, whether
+    // some of its parts did not come together, and (sticky) the lattices
+    // swept by one workgroup for that reason
+    uint32_t ticket, crowded, alone;
 };
 
 // One persistent launch: n_mcs MCS of a batch (every activation, then the
@@ -201,7 +204,11 @@ struct PersistentLaunch {
 constexpr int kResidentMaxThreads = 1024;
 constexpr int kResidentQueue = 1024;         // attempts queued for evaluation per workgroup
 constexpr int kResidentList = 192;           // accepted copies listed in LDS per activation
-constexpr int kResidentArrivalStride = 32;   // one cache line of arrivals per lattice
+// Per lattice, in a cache line of its own: the arrivals of its parts at their
+// meetings, and how many have come together (kResidentAlone: they did not).
+// Zero before and after a launch.
+constexpr int kResidentArrivalStride = 32;
+constexpr uint32_t kResidentAlone = 1u << 31;
 // LDS of a resident workgroup beside what its lattice sizes (resident_split)
 constexpr int kResidentStaticLds = 8 * kResidentQueue + 30 * kResidentList + 4 * kMaxTypes * kMaxTypes + 8 * 256 + 1136;
 // Entries of the Act exponential's first table (exp(n / 256)) that the
@@ -220,14 +227,13 @@ struct ResidentSplit {
 };
 struct ResidentLaunch {
     GridBarrier *bar;      // abort and act_overflow
-    uint32_t *arrivals;    // kResidentArrivalStride words per lattice; the first counts arrivals since init
-    uint32_t *ticket;      // NULL: part blockIdx.x
-    uint32_t ticket0;      // the ticket of this launch's first part
-    uint32_t meetings;     // meetings of the parts before this launch
+    uint32_t *arrivals;    // kResidentArrivalStride words per lattice
+    bool meet;             // some lattice has several parts: they are taken by ticket (else part blockIdx.x)
     uint32_t mcs0;
     int32_t n_mcs;
     uint32_t n_act;        // activations per MCS
-    uint32_t spin_limit;   // polls of one wait before giving up
+    uint32_t gather_limit; // polls a part waits for the others of its lattice to start
+    uint32_t spin_limit;   // polls of one wait at a meeting before giving up
     int32_t parity;        // counter buffer the first activation reads
 };
 struct ResidentCall {
@@ -246,6 +252,10 @@ hipError_t launch_resident_u16_3d(const ResidentCall &c, hipStream_t st);
 hipError_t launch_resident_act32_2d(const ResidentCall &c, hipStream_t st);
 hipError_t launch_resident_act32_3d(const ResidentCall &c, hipStream_t st);
 hipError_t launch_resident_act16(const ResidentCall &c, hipStream_t st);
+// After a launch whose parts meet: the lattices whose parts did not come
+// together, swept by one workgroup each, and the launch's counters cleared.
+hipError_t launch_resident_alone(const SweepArgs *args, const int64_t *label_off, int n_lattices, int ndim, bool act,
+                                 const ResidentLaunch &rl, hipStream_t st);
 
 // Per-lattice tables for the summary statistics of a batch (device arrays).
 struct StatsTables {

@@ -1,6 +1,7 @@
 // Sweeps of lattices that stay in LDS from the first activation of a call to
 // its last, compiled once per stored-word type and dimension
-// (CPM_RESIDENT_PART = 0..4).
+// (CPM_RESIDENT_PART = 0..4), and the sweep of a lattice whose parts do not
+// come together (5).
 //
 // An activation launched by itself (cpm_sweep_kernels.hpp) waits for its
 // launch, for a chain of dependent loads of labels and counters, and for the
@@ -33,7 +34,7 @@
 #include "cpm_sweep_kernels.hpp"
 
 #ifndef CPM_RESIDENT_PART
-#error "compile with -DCPM_RESIDENT_PART=<0..4>"
+#error "compile with -DCPM_RESIDENT_PART=<0..5>"
 #endif
 
 namespace cpm {
@@ -281,7 +282,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     };
     // Meeting of a lattice's parts: every wave's stores and atomics complete,
     // then one arrival per part; the count only grows.  The wait is bounded.
-    uint32_t meeting = rl.meetings;
+    uint32_t meeting = 0;
     uint32_t *arrivals = rl.arrivals + (size_t)pt.lattice * kResidentArrivalStride;
     auto arrive = [&]() {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -930,13 +931,51 @@ __global__ void __launch_bounds__(kResidentMaxThreads) resident_kernel(SweepArgs
 // A batch: workgroups take the parts in order (a ticket each), so that the
 // parts a workgroup waits for have been taken or are taken next, whatever
 // the order of dispatch.
+//
+// Parts of one lattice meet only once all of them run, which takes as many
+// free CUs as it has parts: kernels of other streams may hold them for any
+// time.  The parts come together first, before anything is written; if they
+// do not within gather_limit polls (kCrowdedPolls once it has happened in
+// this launch), one of them marks the lattice, all leave it as it is, and
+// alone_kernel sweeps it after this launch.  Either all parts find the count
+// complete or all find the mark: it is set by compare-and-swap on an
+// incomplete count only.
+constexpr uint32_t kCrowdedPolls = 4096;
+constexpr uint32_t kNoPart = 0xFFFFFFFFu;
+__device__ __forceinline__ uint32_t take_part(const ResidentPart *parts, const ResidentLaunch &rl)
+{
+    const uint32_t ticket = atomicAdd(&rl.bar->ticket, 1u);
+    if (ticket >= gridDim.x) return kNoPart;
+    const uint32_t n_parts = (uint32_t)parts[ticket].n_parts;
+    if (n_parts == 1) return ticket;
+    uint32_t *here = rl.arrivals + (size_t)parts[ticket].lattice * kResidentArrivalStride + 1;
+    if (rl.gather_limit == 0) {  // no wait at all: every lattice in parts is marked
+        __hip_atomic_fetch_or(here, kResidentAlone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return kNoPart;
+    }
+    __hip_atomic_fetch_add(here, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (uint32_t polls = 0;;) {
+        uint32_t v = agent_load(here);
+        if (v & kResidentAlone) return kNoPart;
+        if (v == n_parts) return ticket;
+        if (polls < rl.gather_limit && (polls < kCrowdedPolls || (polls & 63u) != 0 || agent_load(&rl.bar->crowded) == 0u)) {
+            ++polls;
+            __builtin_amdgcn_s_sleep(1);
+        } else if (__hip_atomic_compare_exchange_strong(here, &v, v | kResidentAlone, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT)) {
+            agent_store(&rl.bar->crowded, 1u);
+            return kNoPart;
+        }
+    }
+}
+
 template <typename Cell, int D, bool ACT, bool SINGLE, bool K1, bool EXT>
 __global__ void __launch_bounds__(kResidentMaxThreads) batch_resident_kernel(const SweepArgsG *args,
                                                                              const ResidentPart *parts, ResidentLaunch rl)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     int &s_ticket = reinterpret_cast<ResidentShared *>(smem)->go;
-    if (threadIdx.x == 0) s_ticket = (int)(rl.ticket ? atomicAdd(rl.ticket, 1u) - rl.ticket0 : blockIdx.x);
+    if (threadIdx.x == 0) s_ticket = (int)(rl.meet ? take_part(parts, rl) : blockIdx.x);
     __syncthreads();
     const uint32_t ticket = (uint32_t)__builtin_amdgcn_readfirstlane(s_ticket);
     if (ticket >= gridDim.x) return;
@@ -949,6 +988,94 @@ __global__ void __launch_bounds__(kResidentMaxThreads) batch_resident_kernel(con
     ConstArgs &a = ((ConstArgs *)args)[pt.lattice];
     if (pt.n_parts == 1) sweep_resident<Cell, D, ACT, SINGLE, K1, EXT, true>(a, pt, rl);
     else sweep_resident<Cell, D, ACT, SINGLE, K1, EXT, false>(a, pt, rl);
+}
+
+// One activation after another of a lattice whose parts did not come
+// together, on one workgroup, from the caller's labels and activities in
+// global memory.  It runs only where the GPU is crowded, and is written to be
+// short: an accepted copy is a record of its area, added to the counters
+// after the activation.
+template <int D, bool ACT>
+__global__ void __launch_bounds__(kBlock) alone_kernel(const SweepArgs *args, const int64_t *label_off, ResidentLaunch rl)
+{
+    __shared__ int32_t j_lds[kMaxTypes * kMaxTypes];
+    const SweepArgs &a = args[blockIdx.x];
+    const int tid = threadIdx.x;
+    uint32_t *line = rl.arrivals + (size_t)blockIdx.x * kResidentArrivalStride;
+    const bool alone = (line[1] & kResidentAlone) != 0;
+    __syncthreads();
+    if (tid < 2) line[tid] = 0;
+    if (blockIdx.x == 0 && tid == 0) rl.bar->ticket = rl.bar->crowded = 0;
+    if (!alone) return;
+    if (tid == 0) atomicAdd(&rl.bar->alone, 1u);
+
+    const DeviceModel *m = a.model;
+    j_lds[tid] = (int32_t)m->J[tid];
+    static_assert(kMaxTypes * kMaxTypes == kBlock, "one entry of J per thread");
+    const SharedTables tables{j_lds, m->LG, reinterpret_cast<const TypeParams *>(m->lam_v)};
+    const ThrTables tb{m->TM32, m->TL32, m->TI32, m->n_ti};
+    constexpr int NNB = D == 2 ? 8 : 26;
+    const int L0 = a.L[0], L1 = a.L[1], L2 = a.L[2], s = a.s;
+    const LdsMap<kDirect> map{L0, L1, L0, L1, L2};
+    const int areas = a.na[0] * a.na[1] * a.na[2];
+    const uint32_t sd = (uint32_t)(D == 2 ? s * s : s * s * s);
+    int32_t *cnt = a.counters[0];  // both buffers hold the exact state
+    int4 *records = a.dlist[0];    // k per area
+    int32_t *n_records = reinterpret_cast<int32_t *>(a.dlist[1]);
+    uint32_t nontrivial = 0, accepted = 0;
+    auto barrier = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    };
+    barrier();
+    for (int i_mcs = 0; i_mcs < rl.n_mcs; ++i_mcs) {
+        const uint32_t mcs = rl.mcs0 + (uint32_t)i_mcs;
+        for (uint32_t alpha = 0; alpha < rl.n_act; ++alpha) {
+            const int cx = (int)(alpha & 1), cy = (int)((alpha >> 1) & 1), cz = D == 3 ? (int)((alpha >> 2) & 1) : 0;
+            for (int i = tid; i < areas; i += kBlock) {
+                const int ax = i % a.na[0], ay = i / a.na[0] % a.na[1], az = i / a.na[0] / a.na[1];
+                int4 *own = records + (size_t)i * a.k;
+                int n_own = 0;
+                for (int j = 0; j < a.k; ++j) {
+                    const uint4 u = philox4x32_10(make_uint4((uint32_t)i, mcs, (alpha << 8) | (uint32_t)j, a.lattice_id), a.key0, a.key1);
+                    const int o = (int)__umulhi(u.x, sd);
+                    const int tx = s * (2 * ax + cx) + o % s, ty = s * (2 * ay + cy) + o / s % s;
+                    const int tz = D == 3 ? s * (2 * az + cz) + o / s / s : 0;
+                    const int nsel = (int)__umulhi(u.y, (uint32_t)NNB);
+                    const int sx = tx + nb_dx<D>(nsel), sy = ty + nb_dy<D>(nsel), sz = tz + nb_dz<D>(nsel);
+                    const int t = map.at(tx, ty, tz), src = map.at(sx, sy, sz);
+                    const int lt = a.lat[t], ls = a.lat[src];
+                    if (lt == ls || lt < 0 || ls < 0) continue;
+                    ++nontrivial;
+                    const int tt = lt == 0 ? 0 : a.cell_type[lt], ts = ls == 0 ? 0 : a.cell_type[ls];
+                    int64_t dso, dsn;
+                    if (!evaluate<int32_t, D, ACT, false, kDirect, true>(
+                            a, tb, JRows{}, tables, a.lat, a.act, map, tx, ty, tz, sx, sy, sz, src, lt, ls, tt, ts,
+                            seen_counters(cnt, lt, own, n_own, own + kOwnInRegs),
+                            seen_counters(cnt, ls, own, n_own, own + kOwnInRegs), u.z, dso, dsn))
+                        continue;
+                    ++accepted;
+                    a.lat[t] = ls;
+                    if (ACT) a.act[t] = (uint8_t)(ls >= 1 ? max(m->max_act[ts], 0) : 0);
+                    own[n_own++] = make_int4(lt, ls, (int)dso, (int)dsn);
+                }
+                n_records[i] = n_own;
+            }
+            barrier();
+            for (int i = tid; i < areas; i += kBlock)
+                for (int j = 0; j < n_records[i]; ++j) add_deltas(cnt, records[(size_t)i * a.k + j]);
+            barrier();
+        }
+        if (ACT) {
+            for (int i = tid; i < L0 * L1 * L2; i += kBlock) a.act[i] = (uint8_t)max((int)a.act[i] - 1, 0);
+            barrier();
+        }
+    }
+    const int64_t n_labels = label_off[blockIdx.x + 1] - label_off[blockIdx.x];
+    for (int64_t i = tid; i < 2 * n_labels; i += kBlock) a.counters[1][i] = cnt[i];
+    atomicAdd(reinterpret_cast<unsigned long long *>(a.stats), (unsigned long long)nontrivial);
+    atomicAdd(reinterpret_cast<unsigned long long *>(a.stats) + 1, (unsigned long long)accepted);
 }
 
 template <typename F>
@@ -1010,6 +1137,19 @@ hipError_t launch_resident_act16(const ResidentCall &c, hipStream_t st)
                     : launch_one<char16_t, 2, true, true, false, false>(c, st);
     return c.k1 ? launch_one<char16_t, 3, true, true, true, false>(c, st)
                 : launch_one<char16_t, 3, true, true, false, false>(c, st);
+}
+#elif CPM_RESIDENT_PART == 5
+hipError_t launch_resident_alone(const SweepArgs *args, const int64_t *label_off, int n_lattices, int ndim, bool act,
+                                 const ResidentLaunch &rl, hipStream_t st)
+{
+    if (ndim == 2) {
+        if (act) alone_kernel<2, true><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
+        else alone_kernel<2, false><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
+    } else {
+        if (act) alone_kernel<3, true><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
+        else alone_kernel<3, false><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
+    }
+    return hipGetLastError();
 }
 #endif
 

@@ -168,3 +168,82 @@ def test_hot_lists_grow_while_drawn_ahead(torch_cuda, s, k):
         lats.append(lat)
         cts.append(np.array([0] + [1] * m, dtype=np.int32))
     _batches_same(torch_cuda, params, lats, cts, "in_place" if k == 1 else "box", 14)
+
+
+def _cut_batch(torch, case):
+    """Parameters, lattices and types of BATCH[case], without chemotaxis."""
+    dims, kind, n, types, s, k, act, _ = BATCH[case]
+    params, lats, cts = [], [], []
+    for i, d in enumerate(dims):
+        lat, m = _lattice(kind, d, n, 80 + i, types == 2)
+        kw = dict(sub=s, attempts=k, lattice_id=i)
+        if act:
+            kw.update(lambda_act=[0, 60.0] + ([0.0, 0.0] if types == 2 else []), max_act=[0, 20] + ([0, 0] if types == 2 else []))
+        if types == 1 and not act:
+            kw.update(lambda_chemotaxis=[0, 9.0], chemotaxis_field=torch.as_tensor(
+                np.random.default_rng(i).integers(-16000, 16000, int(np.prod(d)) * len(d)).astype(np.int16)).cuda())
+        params.append(_params(d, types, 8.0 + i, **kw))
+        lats.append(lat)
+        cts.append(np.array([0] + [1 + (j % types) for j in range(m)], dtype=np.int32))
+    return params, lats, cts
+
+
+def _assert_same(a, b):
+    assert a.torch.equal(a.lattices, b.lattices)
+    assert a.act is None or a.torch.equal(a.act, b.act)
+    for x, y in zip(a.counters(), b.counters()):
+        for lo, hi in zip(a.label_off[:-1], a.label_off[1:]):
+            assert a.torch.equal(x[lo + 1:hi], y[lo + 1:hi])
+    np.testing.assert_array_equal(a.attempt_stats(), b.attempt_stats())
+
+
+@pytest.mark.parametrize("case", [0, 2, 3, 5, 6])
+def test_parts_that_do_not_come_together(torch_cuda, case):
+    # no poll allowed: every lattice cut into parts is marked as not together,
+    # and one workgroup sweeps the lattice; then the parts meet again
+    params, lats, cts = _cut_batch(torch_cuda, case)
+    print(f"parts apart, batch case {BATCH[case]}", flush=True)
+    b, ref = cpm.Batch(params, lats, cts), cpm.Batch(params, lats, cts)
+    ref.use_graph(False)
+    cpm.cpm_batch_set_barrier_spin_limit(b.handle, 0)
+    b.sweep(2)
+    ref.sweep(2)
+    _assert_same(b, ref)
+    apart = cpm.cpm_batch_alone_count(b.handle, b.stream)
+    assert apart > 0
+    cpm.cpm_batch_set_barrier_spin_limit(b.handle, 1 << 21)
+    b.sweep(2)
+    ref.sweep(2)
+    _assert_same(b, ref)
+    assert cpm.cpm_batch_alone_count(b.handle, b.stream) == apart
+    assert all(b.check_invariants())
+
+
+@pytest.mark.parametrize("case", [0, 5])
+def test_captured_sweeps_replay(torch_cuda, case):
+    # a captured sweep of lattices cut into parts, replayed with eager work
+    # and a synchronisation in between
+    torch = torch_cuda
+    params, lats, cts = _cut_batch(torch, case)
+    print(f"captured resident sweeps, batch case {BATCH[case]}", flush=True)
+    b, ref = cpm.Batch(params, lats, cts), cpm.Batch(params, lats, cts)
+    ref.use_graph(False)
+    b.sweep(1)
+    ref.sweep(1)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        b.sweep(2)
+    for _ in range(3):
+        g.replay()
+        ref.mcs = 1
+        ref.sweep(2)
+        torch.cuda.synchronize()
+        assert torch.equal(b.lattices, ref.lattices)
+        assert b.act is None or torch.equal(b.act, ref.act)
+        b.mcs = ref.mcs = 7
+        b.sweep(1)
+        ref.sweep(1)
+        for x, y in zip(b.cell_stats(), ref.cell_stats()):
+            assert torch.equal(x, y)
+    assert all(b.check_invariants())
