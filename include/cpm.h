@@ -313,13 +313,14 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
  * decay and the MCS counter update, kernel nodes only), captured on a private
  * stream and launched on `stream`. */
 int cpm_batch_sweep(cpm_batch *b, int32_t n_mcs, void *stream);
-/* enabled = 0: cpm_batch_sweep launches the same kernels one by one instead
- * of the graph (same results).  Pure host. */
+/* enabled = 0: cpm_batch_sweep launches the graph's kernels one by one (mode
+ * 1 of cpm_batch_launch_mode), else it replays the graph (mode 0); same
+ * results.  Pure host. */
 int cpm_batch_use_graph(cpm_batch *b, int32_t enabled);
 /* How cpm_batch_sweep launches its work (same results in every mode; pure
- * host): 0 = the default (see cpm_batch_sweep: lattices kept in LDS, or one
- * replay of the captured MCS graph per MCS),
- * 1 = the graph's kernels one by one, 2 = one persistent launch per call:
+ * host): 3 = the default (see cpm_batch_sweep: lattices kept in LDS where
+ * that is possible, else mode 0), 0 = one replay of the captured MCS graph
+ * per MCS, 1 = the graph's kernels one by one, 2 = one persistent launch per call:
  * as many workgroups as the GPU holds at once (launched cooperatively, so
  * all are resident) loop over the (lattice, tile) work table and meet at a
  * device-wide barrier after every activation and after every MCS's Act
@@ -328,14 +329,14 @@ int cpm_batch_use_graph(cpm_batch *b, int32_t enabled);
  * in place (k = 1; CPM_ENOTSUP otherwise).  A barrier wait is bounded (see
  * cpm_batch_set_barrier_spin_limit): a launch whose wait runs out ends
  * early and leaves the batch invalid, which cpm_batch_attempt_stats and
- * cpm_batch_check_invariants report as CPM_EDEVICE.  (In mode 0 the parts of
+ * cpm_batch_check_invariants report as CPM_EDEVICE.  (In mode 3 the parts of
  * a lattice come together before they change it: where other streams keep
  * the CUs busy for longer than the limit, the lattice is swept by one
  * workgroup instead, with the same results.) */
 int cpm_batch_launch_mode(cpm_batch *b, int32_t mode);
 /* Polls of one barrier wait before a persistent launch gives up (default
  * 2^20, about a second; a barrier normally completes in microseconds), and of
- * the wait for the parts of a lattice to come together in mode 0 (default
+ * the wait for the parts of a lattice to come together in mode 3 (default
  * 2^21).  Pure host. */
 int cpm_batch_set_barrier_spin_limit(cpm_batch *b, uint32_t polls);
 /* Lattices that sweeps of this batch took on one workgroup because their

@@ -463,7 +463,7 @@ def cpm_batch_occupancy(h: int, d_counts, stream: int) -> None:
     _check(load().cpm_batch_occupancy(h, _ptr(d_counts), stream), "cpm_batch_occupancy")
 
 
-BATCH_MODES = {"graph": 0, "eager": 1, "persistent": 2}
+BATCH_MODES = {"graph": 0, "eager": 1, "persistent": 2, "auto": 3}
 
 
 def cpm_batch_launch_mode(h: int, mode) -> None:
@@ -592,7 +592,8 @@ class Batch:
         cpm_batch_use_graph(self.handle, enabled)
 
     def launch_mode(self, mode) -> None:
-        """"graph" (one graph replay per MCS), "eager" or "persistent"."""
+        """"auto" (the default: lattices kept in LDS where they fit, else
+        "graph"), "graph" (one graph replay per MCS), "eager" or "persistent"."""
         cpm_batch_launch_mode(self.handle, mode)
 
     def lattice(self, i):

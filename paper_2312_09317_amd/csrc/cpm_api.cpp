@@ -95,10 +95,11 @@ struct cpm_batch {
     size_t max_sites = 0;
     int64_t max_bricks = 0;          // largest centroid-reduction grid of the lattices
     bool use_graph = true;
-    int mode = 0;                    // 0: one graph replay per MCS, 1: kernels one by one, 2: persistent launch
+    int mode = 3;                    // 0: one graph replay per MCS, 1: kernels one by one, 2: persistent launch,
+                                     // 3: resident where the batch allows it, else 0
     cpm::GridBarrier *bar = nullptr; // barrier of the persistent launch
     uint32_t spin_limit = 1u << 20;  // polls of a barrier wait before the launch gives up
-    // resident sweeps (mode 0, where every lattice can be cut into few parts)
+    // resident sweeps (mode 3, where every lattice can be cut into few parts)
     bool resident = false;
     const cpm::ResidentPart *d_parts = nullptr;
     std::vector<cpm::ResidentPart> parts;
@@ -1613,7 +1614,7 @@ int stream_cus(hipStream_t st)
 // lattice that meet need a CU each.
 bool resident_on(const cpm_batch *b, hipStream_t st)
 {
-    return b->resident && b->mode == 0 && (b->most_parts == 1 || stream_cus(st) >= b->most_parts);
+    return b->resident && b->mode == 3 && (b->most_parts == 1 || stream_cus(st) >= b->most_parts);
 }
 
 // n_mcs MCS of a batch whose lattices stay in LDS.
@@ -1670,7 +1671,8 @@ int cpm_batch_sweep(cpm_batch *b, int32_t n_mcs, void *stream)
     hipError_t e;
     if (resident_on(b, st)) return batch_sweep_resident(b, n_mcs, n_act, st);
     b->lists_pending = true;
-    if (b->mode == 0 && !b->mcs_graph && (e = capture_mcs(b, n_act)) != hipSuccess)
+    const bool graph = b->mode == 0 || b->mode == 3;
+    if (graph && !b->mcs_graph && (e = capture_mcs(b, n_act)) != hipSuccess)
         return device_fail(e, "capture MCS graph");
     if (b->mirror && (e = cpm::launch_batch_mirror(b->d_args, b->n, b->max_sites, true, st)) != hipSuccess)
         return device_fail(e, "to 16-bit working copy");
@@ -1703,7 +1705,7 @@ int cpm_batch_sweep(cpm_batch *b, int32_t n_mcs, void *stream)
         b->mcs_run += (uint64_t)n_mcs;
     }
     for (int32_t m = 0; m < n_mcs && b->mode != 2; ++m) {
-        e = b->mode == 0 ? hipGraphLaunch(b->mcs_graph, st) : enqueue_mcs(b, n_act, st);
+        e = graph ? hipGraphLaunch(b->mcs_graph, st) : enqueue_mcs(b, n_act, st);
         if (e != hipSuccess) return device_fail(e, "MCS");
         b->activation += n_act;
         ++b->mcs;
@@ -1758,7 +1760,7 @@ int cpm_batch_occupancy(cpm_batch *b, int32_t *d_counts, void *stream)
 int cpm_batch_launch_mode(cpm_batch *b, int32_t mode)
 {
     if (!b) return fail(CPM_EINVAL, "batch is NULL");
-    if (mode < 0 || mode > 2) return fail(CPM_EINVAL, "mode must be 0, 1 or 2");
+    if (mode < 0 || mode > 3) return fail(CPM_EINVAL, "mode must be 0, 1, 2 or 3");
     if (mode == 2 && !(b->k == 1 && b->layout == 2))
         return fail(CPM_ENOTSUP, "the persistent launch runs batches swept in place (k = 1)");
     b->mode = mode;

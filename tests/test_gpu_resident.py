@@ -247,3 +247,44 @@ def test_captured_sweeps_replay(torch_cuda, case):
         for x, y in zip(b.cell_stats(), ref.cell_stats()):
             assert torch.equal(x, y)
     assert all(b.check_invariants())
+
+
+def test_graph_mode_replays_the_graph(torch_cuda):
+    # a batch that the default keeps in LDS: "graph" replays the MCS graph
+    # (no lattice is in parts, so none is swept alone), with read-outs and
+    # serial MCS between replays, and the modes may follow each other
+    params, lats, cts = _cut_batch(torch_cuda, 0)
+    b, ref = cpm.Batch(params, lats, cts), cpm.Batch(params, lats, cts)
+    ref.launch_mode("eager")
+    cpm.cpm_batch_set_barrier_spin_limit(b.handle, 0)
+    for step, mode in enumerate(("graph", "graph", "auto", "eager", "auto", "graph", "auto")):
+        print(f"step {step}: {mode}", flush=True)
+        b.launch_mode(mode)
+        before = cpm.cpm_batch_alone_count(b.handle, b.stream)
+        for x in (b, ref):
+            x.sweep(1 + step % 2)
+        assert (cpm.cpm_batch_alone_count(b.handle, b.stream) > before) == (mode == "auto")
+        for u, v in zip(b.cell_stats(), ref.cell_stats()):
+            assert torch_cuda.equal(u, v)
+        _assert_same(b, ref)
+        if step in (1, 4):
+            b.sweep_serial(1)
+            ref.sweep_serial(1)
+    assert all(b.check_invariants())
+    with pytest.raises(cpm.CpmError) as e:
+        b.launch_mode(4)
+    assert e.value.code == cpm.CPM_EINVAL
+
+
+@pytest.mark.parametrize("case", [3, 6])
+def test_default_mode_after_others(torch_cuda, case):
+    # resident, by launches, and resident again
+    params, lats, cts = _cut_batch(torch_cuda, case)
+    b, ref = cpm.Batch(params, lats, cts), cpm.Batch(params, lats, cts)
+    ref.launch_mode("eager")
+    for mode in ("auto", "graph", "auto", "eager", "auto"):
+        b.launch_mode(mode)
+        b.sweep(2)
+        ref.sweep(2)
+        _assert_same(b, ref)
+    assert all(b.check_invariants())
