@@ -226,8 +226,9 @@ def main():
     ap.add_argument("--batch-max-side", type=int, default=512,
                     help="batch workload: largest side (512 in the benchmark; 64 gives a batch of 64^2 lattices "
                          "whose MCS time is mostly launch or barrier overhead)")
-    ap.add_argument("--batch-mode", default=None, choices=("graph", "eager", "persistent"),
-                    help="batch workload: how each sweep is launched (default: the tuner's choice, else graph)")
+    ap.add_argument("--batch-mode", default=None, choices=("auto", "graph", "eager", "persistent"),
+                    help="batch workload: how each sweep is launched (default: the tuner's choice, else auto with "
+                         "--layout auto and graph with a named layout)")
     ap.add_argument("--order-densities", default="0.1,0.2,0.3,0.4,0.5,0.6,0.7,0.8,0.9",
                     help="collective-order workload: cell densities")
     ap.add_argument("--order-side", type=int, default=128, help="collective-order workload: lattice side")
@@ -696,9 +697,10 @@ def bench_polarisation(args):
 
 def bench_batch(args):
     """512 independent 2D lattices of uneven sizes (64..512, 30% cells, Act
-    term, per-lattice parameters), advanced together: one launch per
-    activation, each MCS one replay of a captured HIP graph.  Step = 1 MCS
-    of every lattice."""
+    term, per-lattice parameters), advanced together: kept in LDS over a
+    sweep call (the library's choice), or, with a named layout, one launch per
+    activation, each MCS one replay of a captured HIP graph.  Step = 1 MCS of
+    every lattice."""
     import torch
     from paper_2312_09317_amd import cpm, inputs
     ws = inputs.config3(n_lattices=args.batch_n, seed=1, n_mcs=args.steps, L_max=args.batch_max_side)
@@ -706,8 +708,8 @@ def bench_batch(args):
     log(f"batch of {len(ws)} lattices, {sites} sites")
     params = [cpm.Params.from_workload(w) for w in ws]
     lattices, types = [w.lattice for w in ws], [w.cell_type for w in ws]
-    cfg = {"layout": "in_place" if args.layout in ("tune", "auto") else args.layout, "tiles": ["auto"] * len(ws),
-           "mode": args.batch_mode or "graph"}
+    cfg = {"layout": args.layout, "tiles": ["auto"] * len(ws),
+           "mode": args.batch_mode or ("auto" if args.layout == "auto" else "graph")}
     tuning = None
     if args.layout == "tune":
         r = cpm.autotune_batch(params, lattices, types, trial_mcs=args.tune_mcs, log=log)
@@ -754,7 +756,8 @@ def bench_batch(args):
                    "attempts_per_activation": ws[0].k, "act": True, "launch": tuned, "tuning_ms_per_mcs": tuning,
                    "label_storage": "uint16 words: label + 1 and activity (one cell type, at most 2,046 cells, "
                                     "Max_act <= 31), written from the int32 lattices and activities per sweep call"},
-        "roofline": roofline_fields(achieved, batch_traffic, avg_launch_s, "batch_sweep_kernel",
+        "roofline": roofline_fields(achieved, batch_traffic, avg_launch_s,
+                                    "batch_resident_kernel" if cfg["mode"] == "auto" else "batch_sweep_kernel",
                                     bytes_per_attempt(2, ws[0].s, ws[0].k, acc, act=True)),
         "cpu_baseline": cpu_fields(cpu), "cpu_baseline_threads": cpu_fields(cpu_threads)}), flush=True)
 

@@ -674,11 +674,12 @@ class Batch:
 
 def tuning_candidates(params: Params, n_cells: int):
     """(layout, tile, tile order) triples worth timing for this model: the
-    library's choice of each layout that fits, in-place tiles of other
-    shapes, and in 3D the same in-place tiles taken in bricks."""
+    library's choice first (small lattices it keeps in LDS, which no named
+    layout does), then its tiles of each layout that fits, in-place tiles of
+    other shapes, and in 3D the same in-place tiles taken in bricks."""
     c = params.c
     na = [c.dims[d] // (2 * c.sub) if d < c.ndim else 1 for d in range(3)]
-    out, seen = [], set()
+    out, seen = [("auto", (0, 0, 0), "auto")], set()
 
     def add(lay, tile, order="linear"):
         p = params.replace(layout=lay, tile=tile, tile_order=order)
@@ -777,10 +778,12 @@ def autotune_batch(params, lattices, cell_types, acts=None, trial_mcs=3, device=
     """Time launch configurations of a batch and return the fastest.
 
     Candidates (each on a fresh copy of the batch, one warm-up MCS, then
-    trial_mcs timed MCS): the in-place layout with each tile rule of
+    trial_mcs timed MCS): the library's choice (which keeps lattices in LDS
+    where they fit), the in-place layout with each tile rule of
     BATCH_TILE_RULES for every lattice, the staged layouts, then, from the
-    best, one size class (size_classes) at a time given each other tile rule,
-    and the persistent launch.  Every candidate must leave the same lattices
+    best in-place one, one size class (size_classes) at a time given each
+    other tile rule, and the persistent launch.  Every candidate must leave
+    the same lattices
     and activities (results never depend on the launch), else RuntimeError.
     Returns {"best": config, "times": {name: ms per MCS}} with config =
     {"layout", "tiles" (one rule name per lattice), "mode"}; apply it with
@@ -821,16 +824,17 @@ def autotune_batch(params, lattices, cell_types, acts=None, trial_mcs=3, device=
         say(f"autotune_batch: {name} {ms:.3f} ms per MCS")
         return ms
 
-    best_cfg, best_ms = None, None
+    best = {"any": (None, None), "in_place": (None, None)}  # (configuration, ms), of all and of the in-place ones
 
     def consider(name, cfg):
         # the first configuration (the library's choice) is replaced only by
         # one at least TUNE_MARGIN faster
-        nonlocal best_cfg, best_ms
         ms = trial(name, cfg)
-        if ms is not None and (best_ms is None or ms < best_ms * (1.0 - TUNE_MARGIN)):
-            best_cfg, best_ms = cfg, ms
+        for group in ("any", "in_place") if cfg["layout"] == "in_place" else ("any",):
+            if ms is not None and (best[group][1] is None or ms < best[group][1] * (1.0 - TUNE_MARGIN)):
+                best[group] = (cfg, ms)
 
+    consider("auto", {"layout": "auto", "tiles": ["auto"] * n, "mode": "auto"})
     if k1:
         for r in rules:
             consider(f"in_place/{r}/graph", {"layout": "in_place", "tiles": [r] * n, "mode": "graph"})
@@ -838,17 +842,17 @@ def autotune_batch(params, lattices, cell_types, acts=None, trial_mcs=3, device=
             consider(f"{lay}/graph", {"layout": lay, "tiles": ["auto"] * n, "mode": "graph"})
     else:
         consider("box/graph", {"layout": "box", "tiles": ["auto"] * n, "mode": "graph"})
-    if best_cfg["layout"] == "in_place":
+    if best["in_place"][0]:
         for ci, cls in enumerate(size_classes(params)):
             for r in rules:
-                if all(best_cfg["tiles"][i] == r for i in cls):
+                tiles = list(best["in_place"][0]["tiles"])
+                if all(tiles[i] == r for i in cls):
                     continue
-                tiles = list(best_cfg["tiles"])
                 for i in cls:
                     tiles[i] = r
-                consider(f"in_place/class{ci}={r}/graph", dict(best_cfg, tiles=tiles))
-        consider("in_place/best/persistent", dict(best_cfg, mode="persistent"))
-    return {"best": best_cfg, "times": times}
+                consider(f"in_place/class{ci}={r}/graph", dict(best["in_place"][0], tiles=tiles))
+        consider("in_place/best/persistent", dict(best["in_place"][0], mode="persistent"))
+    return {"best": best["any"][0], "times": times}
 
 
 def batch_params(params, cfg):

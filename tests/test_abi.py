@@ -200,3 +200,19 @@ def test_emu_pack_round_trip():
     for l in range(4):
         np.testing.assert_array_equal(W2[l], W[l].astype(np.float32))
         np.testing.assert_array_equal(b2[l], b[l].astype(np.float32))
+
+
+def test_tuning_starts_from_the_librarys_choice():
+    # only the library's own tiling keeps small lattices in LDS: the tuners
+    # have to time it, and first
+    for over in (dict(), dict(attempts=8, sub=4)):
+        p, w = _params(**over)
+        cands = cpm.tuning_candidates(p, w.n_cells)
+        assert cands[0] == ("auto", (0, 0, 0), "auto")
+        assert len(cands) >= 2 and len(set(cands)) == len(cands)
+        lay, tile, order = cands[0]
+        q = p.replace(layout=lay, tile=tile, tile_order=order)
+        assert q.c.layout == 0 and list(q.c.tile) == [0, 0, 0] and q.c.tile_order == 0
+    cfg = {"layout": "auto", "tiles": ["auto"], "mode": "auto"}
+    q = cpm.batch_params([p], cfg)[0]
+    assert q.c.layout == 0 and list(q.c.tile) == [0, 0, 0] and q.c.tile_order == 0

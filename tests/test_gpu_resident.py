@@ -288,3 +288,20 @@ def test_default_mode_after_others(torch_cuda, case):
         ref.sweep(2)
         _assert_same(b, ref)
     assert all(b.check_invariants())
+
+
+@pytest.mark.parametrize("s,k", [(2, 1), (4, 8)])
+def test_batch_tuner_times_the_default(torch_cuda, s, k):
+    ws = inputs.config3(n_lattices=6, L_min=64, L_max=128, seed=5, n_mcs=0)
+    for w in ws:
+        side = w.dims[0] // (2 * s) * (2 * s)
+        w.lattice = w.lattice.reshape(w.dims[1], w.dims[0])[:side, :side].copy().reshape(-1)
+        w.dims = (side, side, 1)
+    params = [cpm.Params.from_workload(w, sub=s, attempts=k) for w in ws]
+    r = cpm.autotune_batch(params, [w.lattice for w in ws], [w.cell_type for w in ws], trial_mcs=2)
+    print(r["times"], flush=True)
+    assert next(iter(r["times"])) == "auto" and len(r["times"]) >= 2
+    b = cpm.Batch(cpm.batch_params(params, r["best"]), [w.lattice for w in ws], [w.cell_type for w in ws])
+    b.launch_mode(r["best"]["mode"])
+    b.sweep(1)
+    assert all(b.check_invariants())
