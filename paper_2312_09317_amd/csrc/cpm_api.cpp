@@ -339,8 +339,9 @@ bool tile_geometry(const cpm_params *p, bool mirror, int force_layout, cpm::Tile
 // when more than max_parts are needed.
 constexpr int kResidentMaxAreas = 32 * 512;  // a thread keeps a bit per attempt of an activation
 constexpr int kResidentBatchParts = 16;      // most parts of a batch's lattice
-constexpr size_t kResidentCUs = 256;         // of the MI355X: one resident workgroup each
 constexpr int kResidentFine = 1700;          // areas per part below which finer cuts no longer pay
+constexpr size_t kResidentAreasPerCU = 1170; // of a batch, per round of its parts over the CUs, from which it pays
+constexpr int kResidentCutAreas = 2000;      // areas per part up to which cut Act lattices pay however few they are
 constexpr size_t kResidentBudget = kLdsLimit - cpm::kResidentStaticLds;
 bool resident_split(const cpm_params *p, size_t cell, int32_t n_labels, int32_t n_ti, size_t budget, int max_parts, int max_areas,
                     cpm::ResidentSplit &sp, size_t &lds, int &areas)
@@ -405,14 +406,59 @@ bool library_tiling(const cpm_params *p)
 
 // Thread areas up to which one lattice sweeps faster in the LDS of a single
 // workgroup than by a launch per activation, which costs 5.5 to 6 us however
-// small it is (us per 4 MCS, resident : launches): 2D k = 1, 224^2 (3,136
-// areas) 322 : 385, 256^2 451 : 382; 2D k = 4, 144^2 (1,296) 276 : 301,
-// 160^2 310 : 309; 3D k = 1, 40^3 (1,000, the most the LDS holds) 1,254 :
-// 1,457; 3D k = 8 loses from 28^3 on (916 : 799).
+// small it is.  The more attempts per activation, the less often it costs
+// that; and the larger s, or the denser the cells, the fewer areas hold one
+// label only.  us per 4 MCS, resident : launches, at a quarter of the sites in
+// cells: 2D k = 1, 208^2 (2,704 areas) 322 : 385, 256^2 451 : 382 (90% in
+// cells: 224^2 433 : 398); s = 2, 144^2 (1,296): k = 2 208 : 375, 128^2
+// (1,024): k = 4 191 : 282 (90%: 291 : 275), 160^2 310 : 309 (346 : 284);
+// s = 3 k = 3, 156^2 (676) 328 : 477, 204^2 (1,156) 525 : 482; s = 4 k = 4,
+// 96^2 (144) 460 : 594, 128^2 (256) 703 : 670; s = 8 k = 4, 64^2 2,218 :
+// 1,805; s = 3 k = 9, 72^2 277 : 260; s = 4 k = 8, 64^2 594 : 415, 144^2 744 :
+// 544.  With the Act term, which launches evaluate from global memory or
+// stage with the labels: k = 4, 144^2 343 : 482 (90%: 160^2 484 : 429); s = 4,
+// 128^2: k = 8 995 : 1,492, k = 16 1,060 : 1,269.  3D k = 1, 40^3 (1,000, the
+// most the LDS holds) 1,254 : 1,457; 3D k = 8 loses from 28^3 on (916 : 799).
 int resident_areas(const cpm_params *p)
 {
-    if (p->ndim == 3) return p->attempts == 1 ? 1280 : 0;
-    return p->attempts == 1 ? 3136 : 1296;
+    const int k = p->attempts, s = p->sub;
+    if (p->ndim == 3) return k == 1 ? 1280 : 0;
+    if (k == 1) return 2704;
+    if (p->act_enabled || k == 2) return 1300;
+    return k > 4 ? 0 : s <= 3 ? 1024 : s == 4 ? 200 : 0;
+}
+
+// Whether a batch (of parameters like p) sweeps faster in LDS, on one
+// workgroup per part, than by a launch per activation over all CUs; areas:
+// those of its largest part, all_areas: of the batch.  Measured on lattices of
+// one size (a quarter of the sites in cells), us per 4 MCS, resident :
+// launches:
+//   3D lattices in parts meet after activations too short for it: 8 of 64^3
+//   2,088 : 1,574, 128 4,221 : 3,735; 32 of 96^3 4,529 : 2,931; Act, 128 of
+//   64^3 11,718 : 5,448.  So do 2D ones on 32-bit words with k = 1 (several
+//   types and the Act term): 32 of 256^2 614 : 579, 128 of 512^2 4,674 :
+//   2,720; but with k = 4 16 of 512^2 501 : 1,145, 128 3,045 : 5,413.
+//   Act lattices in small parts with a CU each pay however few they are: one
+//   of 512^2 (16 parts of 1,024 areas) 491 : 508, of 800^2 (12 of 3,400) 601 :
+//   525, but 8 of 800^2 602 : 727; s = 4, 100 of 400^2 (300 parts of 833)
+//   3,618 : 2,686.
+//   Uncut lattices up to resident_areas pay likewise: one of 160^2 269 : 405,
+//   128 278 : 454; one of 40^3 1,227 : 1,590, 256 1,247 : 1,947.
+//   Else an activation with k = 1 takes 6 to 7.5 us per round of parts over
+//   the CUs, and by a launch 5.7 us and 9.3 per million areas: 64 of 256^2
+//   (262,144 areas) 493 : 461, 96 493 : 515; 16 of 512^2 (266,240) 487 : 485,
+//   32 496 : 614, 64 (two rounds) 890 : 911; s = 4, 100 of 400^2 (250,000, two
+//   rounds) 3,060 : 1,755.
+//   With k > 1 parts pay from about a third of the CUs on: k = 4, 8 of 512^2
+//   (40 parts) 362 : 319, 16 364 : 437; s = 4 k = 8, 64 of 128^2 791 : 723, 128
+//   795 : 1,190; 32 of 256^2 1,051 : 759, 128 1,055 : 2,248; 16 of 512^2 (64
+//   parts) 913 : 820, 32 912 : 1,553.
+bool resident_pays(const cpm_params *p, bool words32, bool cut, int areas, size_t parts, size_t all_areas, size_t cus)
+{
+    if (cut && (p->ndim == 3 || (words32 && p->attempts == 1))) return false;
+    if (cut ? p->act_enabled && areas <= kResidentCutAreas && parts <= cus : areas <= resident_areas(p)) return true;
+    if (p->attempts > 1) return 3 * parts >= cus;
+    return all_areas >= kResidentAreasPerCU * cus * ((parts + cus - 1) / cus);
 }
 
 // The layout the parameters ask for (0 in cpm_params = the library's choice).
@@ -1448,22 +1494,24 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
     L.ext = false;
     for (const SweepArgs &a : b->args) L.ext = L.ext || a.chem != nullptr;
     L.layout = b->layout;
-    // resident sweeps: where the library chooses the tiling and every
-    // lattice can be cut into few parts.  A few large lattices, though, leave
-    // most of the GPU idle that way, and sweep faster by a launch per
-    // activation over all of it (us for one sample and 4 MCS, resident :
-    // launches, uncut): 8 of 256^2 644 : 604, 32 of 256^2 644 : 758; 8 of 64..512
-    // per side 696 : 647, 16 713 : 714, 32 762 : 822, 512 of 160..512 5,134 : 6,561.
+    // resident sweeps: where the library chooses the tiling, every lattice
+    // can be cut into few parts, and that pays (resident_pays)
     b->resident = (b->act16 || b->act_words || b->mirror) && !(b->ndim == 3 && b->k > 1);
     for (int32_t i = 0; i < n && b->resident; ++i) b->resident = library_tiling(&params[i]);
     if (b->resident) {
         const size_t cell = b->act16 || b->mirror ? 2 : 4;
         struct Cut { cpm::ResidentSplit sp; int32_t i; int areas; };
         std::vector<Cut> cuts;
-        int max_areas = 1;
-        // Act batches whose lattices do not fill the GPU are cut finer, as
-        // long as every part has a CU of its own: their cells disperse, and a
-        // part's time goes with its areas (us for two samples and 6 MCS after
+        int max_areas = 1, dev = 0, cus = 0;
+        size_t n_parts = 0, all_areas = 0;
+        if ((e = hipGetDevice(&dev)) != hipSuccess ||
+            (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
+            return device_fail(e, "compute units");
+        // Act batches on 16-bit words whose lattices do not fill the GPU are
+        // cut finer, as long as every part has a CU of its own (on 32-bit
+        // words 64 lattices of 180^2 take 642 us per 4 MCS in three parts
+        // each, 434 uncut): their cells disperse, and a part's time goes with
+        // its areas (us for two samples and 6 MCS after
         // 180 MCS, by launches : uncut : parts of up to 2,048 : 1,024 areas):
         // 100 of 100..256 per side 1,361 : 1,593 : 898 : 842, 64 of 64..512
         // 1,644 : 1,551 : 969 : 952, 16 of 256^2 967 : 931 : 946 : 787, but
@@ -1485,16 +1533,22 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
                 finer.push_back(c);
             }
             if (limit == kResidentMaxAreas) b->resident = fits;
-            else if (!fits || parts > kResidentCUs) break;
+            else if (!fits || parts > (size_t)cus) break;
             cuts.swap(finer);
             b->resident_lds = lds_max;
             max_areas = most;
-            if (!b->act || most <= kResidentFine) break;
+            n_parts = parts;
+            if (!b->act16 || most <= kResidentFine) break;
         }
         b->resident_threads = resident_threads(max_areas);
         bool cut = false;
-        for (const Cut &c : cuts) cut = cut || c.sp.parts[0] * c.sp.parts[1] > 1;
-        if (max_areas > 2000 && sites < (cut ? (size_t)1500000 : (size_t)750000)) b->resident = false;
+        for (const Cut &c : cuts) {
+            const SweepArgs &a = b->args[c.i];
+            cut = cut || c.sp.parts[0] * c.sp.parts[1] > 1;
+            all_areas += (size_t)a.na[0] * a.na[1] * a.na[2];
+        }
+        b->resident = b->resident && resident_pays(&params[0], b->act_words && !b->act16, cut, max_areas, n_parts, all_areas,
+                                                      (size_t)cus);
         // the parts that take longest first
         std::stable_sort(cuts.begin(), cuts.end(), [](const Cut &x, const Cut &y) {
             const bool mx = x.sp.parts[0] * x.sp.parts[1] > 1, my = y.sp.parts[0] * y.sp.parts[1] > 1;

@@ -170,19 +170,36 @@ def test_hot_lists_grow_while_drawn_ahead(torch_cuda, s, k):
     _batches_same(torch_cuda, params, lats, cts, "in_place" if k == 1 else "box", 14)
 
 
+# batches that the default keeps in LDS in parts
+CUT = [
+    ([(640, 512), (288, 300), (64, 48)] * 2, "blobs", 700, 1, 2, 1, True, False),  # 16-bit label-activity words
+    ([(512, 512), (480, 528)] * 2, "blobs", 700, 2, 2, 4, True, False),            # 32-bit words, several types
+    ([(512, 512)] * 2, "blobs", 700, 1, 2, 2, True, True),                         # 32-bit words, one type
+    ([(576, 576)] * 18, "blobs", 500, 1, 4, 8, False, True),
+    ([(512, 528), (640, 600)] * 10, "noise", 900, 2, 2, 1, False, False),
+    ([(640, 700)] * 3, "noise", 400, 1, 1, 1, False, True),
+]
+
+
 def _cut_batch(torch, case):
-    """Parameters, lattices and types of BATCH[case], without chemotaxis."""
-    dims, kind, n, types, s, k, act, _ = BATCH[case]
-    params, lats, cts = [], [], []
+    """Parameters, lattices and types of CUT[case]."""
+    return _batch_of(torch, CUT[case])
+
+
+def _batch_of(torch, spec):
+    dims, kind, n, types, s, k, act, chem = spec
+    params, lats, cts, made = [], [], [], {}
     for i, d in enumerate(dims):
-        lat, m = _lattice(kind, d, n, 80 + i, types == 2)
+        if d not in made:  # lattices of one shape start alike
+            made[d] = _lattice(kind, d, n, 80 + i, types == 2)
+        lat, m = made[d]
         kw = dict(sub=s, attempts=k, lattice_id=i)
         if act:
             kw.update(lambda_act=[0, 60.0] + ([0.0, 0.0] if types == 2 else []), max_act=[0, 20] + ([0, 0] if types == 2 else []))
-        if types == 1 and not act:
+        if chem:
             kw.update(lambda_chemotaxis=[0, 9.0], chemotaxis_field=torch.as_tensor(
                 np.random.default_rng(i).integers(-16000, 16000, int(np.prod(d)) * len(d)).astype(np.int16)).cuda())
-        params.append(_params(d, types, 8.0 + i, **kw))
+        params.append(_params(d, types, 8.0 + i % 6, **kw))
         lats.append(lat)
         cts.append(np.array([0] + [1 + (j % types) for j in range(m)], dtype=np.int32))
     return params, lats, cts
@@ -197,12 +214,12 @@ def _assert_same(a, b):
     np.testing.assert_array_equal(a.attempt_stats(), b.attempt_stats())
 
 
-@pytest.mark.parametrize("case", [0, 2, 3, 5, 6])
+@pytest.mark.parametrize("case", range(len(CUT)))
 def test_parts_that_do_not_come_together(torch_cuda, case):
     # no poll allowed: every lattice cut into parts is marked as not together,
     # and one workgroup sweeps the lattice; then the parts meet again
     params, lats, cts = _cut_batch(torch_cuda, case)
-    print(f"parts apart, batch case {BATCH[case]}", flush=True)
+    print(f"parts apart, case {case}", flush=True)
     b, ref = cpm.Batch(params, lats, cts), cpm.Batch(params, lats, cts)
     ref.use_graph(False)
     cpm.cpm_batch_set_barrier_spin_limit(b.handle, 0)
@@ -219,13 +236,13 @@ def test_parts_that_do_not_come_together(torch_cuda, case):
     assert all(b.check_invariants())
 
 
-@pytest.mark.parametrize("case", [0, 5])
+@pytest.mark.parametrize("case", [0, 3])
 def test_captured_sweeps_replay(torch_cuda, case):
     # a captured sweep of lattices cut into parts, replayed with eager work
     # and a synchronisation in between
     torch = torch_cuda
     params, lats, cts = _cut_batch(torch, case)
-    print(f"captured resident sweeps, batch case {BATCH[case]}", flush=True)
+    print(f"captured resident sweeps, case {case}", flush=True)
     b, ref = cpm.Batch(params, lats, cts), cpm.Batch(params, lats, cts)
     ref.use_graph(False)
     b.sweep(1)
@@ -276,7 +293,7 @@ def test_graph_mode_replays_the_graph(torch_cuda):
     assert e.value.code == cpm.CPM_EINVAL
 
 
-@pytest.mark.parametrize("case", [3, 6])
+@pytest.mark.parametrize("case", range(1, len(CUT)))
 def test_default_mode_after_others(torch_cuda, case):
     # resident, by launches, and resident again
     params, lats, cts = _cut_batch(torch_cuda, case)
@@ -305,3 +322,29 @@ def test_batch_tuner_times_the_default(torch_cuda, s, k):
     b.launch_mode(r["best"]["mode"])
     b.sweep(1)
     assert all(b.check_invariants())
+
+
+@pytest.mark.parametrize("spec", [
+    ([(64, 72, 80)] * 2, "blobs", 300, 2, 2, 1, False, False),   # 3D lattices in parts
+    ([(512, 512)] * 2, "blobs", 700, 2, 2, 1, True, False),      # 32-bit words, one attempt
+    ([(576, 576)] * 2, "blobs", 500, 1, 4, 8, False, True),      # too few parts for the CUs
+    ([(512, 528)] * 2, "noise", 900, 1, 2, 1, False, False),
+])
+def test_batches_swept_faster_by_launches(torch_cuda, spec):
+    # these leave the LDS path to the graph: no lattice of theirs is in parts
+    params, lats, cts = _batch_of(torch_cuda, spec)
+    b, ref = cpm.Batch(params, lats, cts), cpm.Batch(params, lats, cts)
+    ref.launch_mode("eager")
+    cpm.cpm_batch_set_barrier_spin_limit(b.handle, 0)
+    b.sweep(2)
+    ref.sweep(2)
+    _assert_same(b, ref)
+    assert cpm.cpm_batch_alone_count(b.handle, b.stream) == 0
+
+
+def test_many_attempts_per_area_uncut(torch_cuda):
+    # eight attempts per area, nearly all of them evaluated and many accepted
+    spec = ([(96, 64)] * 100, "noise", 500, 2, 4, 8, False, False)
+    params, lats, cts = _batch_of(torch_cuda, spec)
+    params = [p.replace(temperature=40.0) for p in params]
+    _batches_same(torch_cuda, params, lats, cts, "box", 4)
