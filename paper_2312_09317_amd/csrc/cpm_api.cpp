@@ -371,27 +371,23 @@ bool resident_split(const cpm_params *p, size_t cell, int32_t n_labels, int32_t 
     else lds = budget + 1;
     if (s > 15) return false;  // the kernel divides draws by s in 16 bits
     if (lds <= budget && (int64_t)na0 * na1 * na2 <= max_areas) {
-        sp = cpm::ResidentSplit{{na1, na2}, {1, 1}, (int32_t)cap};
+        sp = cpm::ResidentSplit{na1, 1, (int32_t)cap};
         areas = na0 * na1 * na2;
         return true;
     }
+    if (p->ndim == 3) return false;
     int best = 0;
-    for (int q2 = 1; q2 <= std::min(na2, max_parts); ++q2)
-        for (int q1 = 1; q1 <= std::min(na1, max_parts / q2); ++q1) {
-            const int T1 = (na1 + q1 - 1) / q1, T2 = (na2 + q2 - 1) / q2;
-            const int n1 = (na1 + T1 - 1) / T1, n2 = (na2 + T2 - 1) / T2;
-            if (n1 * n2 < 2) continue;
-            const size_t b1 = 2 * (size_t)s * T1 + (n1 > 1 ? R : 0);
-            const size_t b2 = p->ndim == 3 ? 2 * (size_t)s * T2 + (n2 > 1 ? R : 0) : 1;
-            const int64_t ar = (int64_t)na0 * T1 * T2;
-            const size_t bytes = up16((size_t)p->dims[0] * b1 * b2 * cell) + tables + heads(ar) + bits(ar) + lists(p->ndim == 2 ? (ar + 1) / 2 : 0);
-            if (bytes > budget || ar > max_areas) continue;
-            if (best && (n1 * n2 > best || (n1 * n2 == best && bytes >= lds))) continue;
-            best = n1 * n2;
-            lds = bytes;
-            areas = (int)ar;
-            sp = cpm::ResidentSplit{{T1, T2}, {n1, n2}, p->ndim == 2 ? (int32_t)((ar + 1) / 2) : 0};
-        }
+    for (int q = 2; q <= std::min(na1, max_parts); ++q) {
+        const int T = (na1 + q - 1) / q, n = (na1 + T - 1) / T;
+        const int64_t ar = (int64_t)na0 * T;
+        const size_t bytes = up16((size_t)p->dims[0] * (2 * (size_t)s * T + R) * cell) + tables + heads(ar) + bits(ar) + lists((ar + 1) / 2);
+        if (n < 2 || bytes > budget || ar > max_areas) continue;
+        if (best && (n > best || (n == best && bytes >= lds))) continue;
+        best = n;
+        lds = bytes;
+        areas = (int)ar;
+        sp = cpm::ResidentSplit{T, n, (int32_t)((ar + 1) / 2)};
+    }
     return best > 0;
 }
 
@@ -433,11 +429,12 @@ int resident_areas(const cpm_params *p)
 // those of its largest part, all_areas: of the batch.  Measured on lattices of
 // one size (a quarter of the sites in cells), us per 4 MCS, resident :
 // launches:
-//   3D lattices in parts meet after activations too short for it: 8 of 64^3
-//   2,088 : 1,574, 128 4,221 : 3,735; 32 of 96^3 4,529 : 2,931; Act, 128 of
-//   64^3 11,718 : 5,448.  So do 2D ones on 32-bit words with k = 1 (several
-//   types and the Act term): 32 of 256^2 614 : 579, 128 of 512^2 4,674 :
-//   2,720; but with k = 4 16 of 512^2 501 : 1,145, 128 3,045 : 5,413.
+//   3D lattices are not cut into parts (cut across y and z they took: 8 of
+//   64^3 2,088 : 1,574, 128 4,221 : 3,735; 32 of 96^3 4,529 : 2,931; Act, 128
+//   of 64^3 11,718 : 5,448).  2D ones on 32-bit words with k = 1 (several
+//   types and the Act term) lose in parts too: 32 of 256^2 614 : 579, 128 of
+//   512^2 4,674 : 2,720; but with k = 4 16 of 512^2 501 : 1,145, 128 3,045 :
+//   5,413.
 //   Act lattices in small parts with a CU each pay however few they are: one
 //   of 512^2 (16 parts of 1,024 areas) 491 : 508, of 800^2 (12 of 3,400) 601 :
 //   525, but 8 of 800^2 602 : 727; s = 4, 100 of 400^2 (300 parts of 833)
@@ -455,7 +452,7 @@ int resident_areas(const cpm_params *p)
 //   parts) 913 : 820, 32 912 : 1,553.
 bool resident_pays(const cpm_params *p, bool words32, bool cut, int areas, size_t parts, size_t all_areas, size_t cus)
 {
-    if (cut && (p->ndim == 3 || (words32 && p->attempts == 1))) return false;
+    if (cut && words32 && p->attempts == 1) return false;
     if (cut ? p->act_enabled && areas <= kResidentCutAreas && parts <= cus : areas <= resident_areas(p)) return true;
     if (p->attempts > 1) return 3 * parts >= cus;
     return all_areas >= kResidentAreasPerCU * cus * ((parts + cus - 1) / cus);
@@ -975,7 +972,7 @@ int init_impl(const cpm_params *params, int32_t *d_lattice, const int32_t *d_cel
         h->resident = resident_split(params, h->words == cpm::kWords16 ? 2 : 4, n_cells + 1, h->host_model->n_ti,
                                      kResidentBudget, 1, kResidentMaxAreas, sp, h->resident_lds, areas) &&
                       areas <= resident_areas(params);
-        h->whole = cpm::ResidentPart{0, 1, 0, sp.T[0], 0, sp.T[1], n_cells + 1, sp.hot_cap};
+        h->whole = cpm::ResidentPart{0, 1, 0, sp.T, n_cells + 1, sp.hot_cap};
         h->resident_threads = resident_threads(areas);
     }
     *out = h.release();
@@ -1529,7 +1526,7 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
                                       kResidentBatchParts, limit, c.sp, bytes, c.areas);
                 lds_max = std::max(lds_max, bytes);
                 most = std::max(most, c.areas);
-                parts += (size_t)(c.sp.parts[0] * c.sp.parts[1]);
+                parts += (size_t)c.sp.parts;
                 finer.push_back(c);
             }
             if (limit == kResidentMaxAreas) b->resident = fits;
@@ -1544,29 +1541,27 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
         bool cut = false;
         for (const Cut &c : cuts) {
             const SweepArgs &a = b->args[c.i];
-            cut = cut || c.sp.parts[0] * c.sp.parts[1] > 1;
+            cut = cut || c.sp.parts > 1;
             all_areas += (size_t)a.na[0] * a.na[1] * a.na[2];
         }
         b->resident = b->resident && resident_pays(&params[0], b->act_words && !b->act16, cut, max_areas, n_parts, all_areas,
                                                       (size_t)cus);
         // the parts that take longest first
         std::stable_sort(cuts.begin(), cuts.end(), [](const Cut &x, const Cut &y) {
-            const bool mx = x.sp.parts[0] * x.sp.parts[1] > 1, my = y.sp.parts[0] * y.sp.parts[1] > 1;
+            const bool mx = x.sp.parts > 1, my = y.sp.parts > 1;
             return mx != my ? mx : x.areas > y.areas;
         });
         if (b->resident) {
             for (const Cut &c : cuts) {
                 const SweepArgs &a = b->args[c.i];
-                const int q = c.sp.parts[0] * c.sp.parts[1];
+                const int q = c.sp.parts;
                 b->most_parts = std::max(b->most_parts, q);
                 for (int j = 0; j < q; ++j) {
                     cpm::ResidentPart pt{};
                     pt.lattice = c.i;
                     pt.n_parts = q;
-                    pt.a1 = j % c.sp.parts[0] * c.sp.T[0];
-                    pt.n1 = std::min(c.sp.T[0], a.na[1] - pt.a1);
-                    pt.a2 = j / c.sp.parts[0] * c.sp.T[1];
-                    pt.n2 = std::min(c.sp.T[1], a.na[2] - pt.a2);
+                    pt.a1 = j * c.sp.T;
+                    pt.n1 = std::min(c.sp.T, a.na[1] - pt.a1);
                     pt.n_labels = n_cells[c.i] + 1;
                     pt.hot_cap = c.sp.hot_cap;
                     b->parts.push_back(pt);
@@ -1699,7 +1694,7 @@ int batch_sweep_resident(cpm_batch *b, int32_t n_mcs, uint32_t n_act, hipStream_
             : b->act_words ? (d2 ? cpm::launch_resident_act32_2d(c, st) : cpm::launch_resident_act32_3d(c, st))
                            : (d2 ? cpm::launch_resident_u16_2d(c, st) : cpm::launch_resident_u16_3d(c, st));
         if (e == hipSuccess && b->most_parts > 1)
-            e = cpm::launch_resident_alone(b->d_args, b->stats_tables.label_off, b->n, b->ndim, b->act, c.launch, st);
+            e = cpm::launch_resident_alone(b->d_args, b->stats_tables.label_off, b->n, b->act, c.launch, st);
         if (e != hipSuccess) return device_fail(e, "resident sweep");
         b->activation += (uint64_t)n_act * (uint64_t)n;
         b->mcs += (uint64_t)n;

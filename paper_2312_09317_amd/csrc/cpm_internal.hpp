@@ -214,15 +214,15 @@ constexpr int kResidentStaticLds = 8 * kResidentQueue + 30 * kResidentList + 4 *
 // Entries of the Act exponential's first table (exp(n / 256)) that the
 // activities of 16-bit words (up to 31) and of 32-bit words (255) can reach.
 constexpr int resident_eh(size_t cell) { return cell == 2 ? 880 : 1420; }
-// One workgroup's share of a lattice: areas [a1, a1 + n1) along y and
-// [a2, a2 + n2) along z, whole rows along x.
+// One workgroup's share of a lattice: all of it, or (2D) areas [a1, a1 + n1)
+// along y, whole rows along x.
 struct ResidentPart {
-    int32_t lattice, n_parts, a1, n1, a2, n2, n_labels;
+    int32_t lattice, n_parts, a1, n1, n_labels;
     int32_t hot_cap;  // room of each colour's list of hot areas (2D)
 };
-// How a lattice is cut: T areas each along y and z (the last ones fewer).
+// How a lattice is cut: parts of T areas along y each (the last one fewer).
 struct ResidentSplit {
-    int32_t T[2], parts[2];
+    int32_t T, parts;
     int32_t hot_cap;
 };
 struct ResidentLaunch {
@@ -254,7 +254,7 @@ hipError_t launch_resident_act32_3d(const ResidentCall &c, hipStream_t st);
 hipError_t launch_resident_act16(const ResidentCall &c, hipStream_t st);
 // After a launch whose parts meet: the lattices whose parts did not come
 // together, swept by one workgroup each, and the launch's counters cleared.
-hipError_t launch_resident_alone(const SweepArgs *args, const int64_t *label_off, int n_lattices, int ndim, bool act,
+hipError_t launch_resident_alone(const SweepArgs *args, const int64_t *label_off, int n_lattices, bool act,
                                  const ResidentLaunch &rl, hipStream_t st);
 
 // Per-lattice tables for the summary statistics of a batch (device arrays).

@@ -10,15 +10,15 @@
 // into LDS as 16- or 32-bit words and runs every activation of the call on
 // it; a barrier of the workgroup takes the place of the launch.
 //
-// A lattice of several parts is cut across y (and z in 3D), whole rows along
-// x.  Its parts meet after every activation: each writes accepted copies
+// A 2D lattice of several parts is cut across y, whole rows along x (3D
+// lattices are swept here uncut or not at all).  Its parts meet after every activation: each writes accepted copies
 // within reach of a cut through to the words in global memory and reads the
 // rows next to its own back from there; cell counters are in global memory.
 // All of that, and the meeting, goes through agent-scope atomic operations,
 // which act where every XCD sees them, so no cache is flushed.  A colour
 // reads across a cut on one side only (the sub-areas of colour bit 0 start
-// at the cut, those of bit 1 end at it): one set of R rows per axis serves
-// both sides, and the box's coordinates wrap at its extent plus R.
+// at the cut, those of bit 1 end at it): one set of R rows serves both sides,
+// and the box's y wraps at its extent plus R.
 //
 // The random draws of an activation depend on its number alone: a thread
 // makes those of the next activation while other waves evaluate this one,
@@ -144,16 +144,15 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     // skip areas whose attempts cannot change anything (below)
     constexpr bool HOT = D == 2 && LONE;
     constexpr bool lone = LONE;
+    static_assert(D == 2 || LONE, "only 2D lattices are cut into parts");
 
     const int tid = threadIdx.x, block = blockDim.x;
     const int s = a.s, L0 = a.L[0], L1 = a.L[1], L2 = a.L[2], na0 = a.na[0], na1 = a.na[1];
     const DeviceModel *model = plain(a.model);
-    const bool cut1 = !LONE && pt.n1 < na1, cut2 = !LONE && D == 3 && pt.n2 < a.na[2];
-    const int y0 = 2 * s * pt.a1, z0 = D == 3 ? 2 * s * pt.a2 : 0;
-    const int N1 = 2 * s * pt.n1, N2 = D == 3 ? 2 * s * pt.n2 : 1;  // own rows, planes
-    const int P1 = N1 + (cut1 ? R : 0), P2 = N2 + (cut2 ? R : 0);   // with the rows across the cut
+    const int y0 = LONE ? 0 : 2 * s * pt.a1, N1 = LONE ? L1 : 2 * s * pt.n1;  // own rows
+    const int P1 = N1 + (LONE ? 0 : R), P2 = L2;                              // with those across the cut
     const LdsMap<kResident> map{L0, P1, L0, P1, P2};
-    const int areas = na0 * pt.n1 * pt.n2;
+    const int n1 = LONE ? na1 : pt.n1, areas = na0 * n1 * (D == 3 ? a.na[2] : 1);
     Cell *lab = reinterpret_cast<Cell *>(smem + kResidentStaticLds);
     unsigned char *sp = smem + kResidentStaticLds + align16(L0 * P1 * P2 * (int)sizeof(Cell));
     // an uncut lattice: both counter buffers in LDS
@@ -212,12 +211,12 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     };
     const bool vec = (L0 & 3) == 0 && (reinterpret_cast<uintptr_t>(lat) & 15) == 0 &&
                      (!ACT || (reinterpret_cast<uintptr_t>(act) & 3) == 0);
-    auto site = [&](int y, int z) { return ((size_t)(z0 + z) * L1 + (size_t)(y0 + y)) * L0; };
+    auto site = [&](int y, int z) { return ((size_t)z * L1 + (size_t)(y0 + y)) * L0; };
     bool over = false;
     {
         const int per = vec ? L0 / 4 : L0;
         const FastDiv by_per((uint32_t)per);
-        for (int c = tid; c < per * N1 * N2; c += block) {
+        for (int c = tid; c < per * N1 * P2; c += block) {
             int ry, rz;
             const int r = (int)by_per.div((uint32_t)c), x = c - r * per;
             own_row(r, ry, rz);
@@ -245,39 +244,18 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     const int pitch32 = L0 / kPer;  // 32-bit words per row (L0 is even)
     const FastDiv by_pitch((uint32_t)pitch32);
     auto publish_edges = [&]() {
-        const int e1 = cut1 ? 2 * R * N2 : 0, e2 = cut2 ? 2 * R * N1 : 0;
-        for (int c = tid; c < (e1 + e2) * pitch32; c += block) {
-            int r = (int)by_pitch.div((uint32_t)c), x = c - r * pitch32, y, z;
-            if (r < e1) {
-                const int q = r % (2 * R);
-                z = r / (2 * R);
-                y = q < R ? q : N1 - 2 * R + q;
-            } else {
-                const int q = (r - e1) % (2 * R);
-                y = (r - e1) / (2 * R);
-                z = q < R ? q : N2 - 2 * R + q;
-            }
-            agent_store(reinterpret_cast<uint32_t *>(words + site(y, z)) + x,
-                        reinterpret_cast<const uint32_t *>(lab + (y + P1 * z) * L0)[x]);
+        for (int c = tid; c < 2 * R * pitch32; c += block) {
+            const int q = (int)by_pitch.div((uint32_t)c), x = c - q * pitch32, y = q < R ? q : N1 - 2 * R + q;
+            agent_store(reinterpret_cast<uint32_t *>(words + site(y, 0)) + x,
+                        reinterpret_cast<const uint32_t *>(lab + y * L0)[x]);
         }
     };
-    // the rows across the cuts that a colour reads, from global memory
-    auto refresh = [&](int cy, int cz) {
-        const int e1 = cut1 ? R * P2 : 0, e2 = cut2 ? R * N1 : 0;
-        for (int c = tid; c < (e1 + e2) * pitch32; c += block) {
-            int r = (int)by_pitch.div((uint32_t)c), x = c - r * pitch32, y, z;
-            if (r < e1) {
-                z = r / R;
-                y = N1 + r % R;
-            } else {
-                y = (r - e1) / R;
-                z = N2 + (r - e1) % R;
-            }
-            const int gy = wrap_once(y0 + (y < N1 ? y : cy ? y : y - N1 - R), L1);
-            const int gz = D == 3 ? wrap_once(z0 + (z < N2 ? z : cz ? z : z - N2 - R), L2) : 0;
-            const size_t g = ((size_t)gz * L1 + gy) * L0;
-            reinterpret_cast<uint32_t *>(lab + (y + P1 * z) * L0)[x] =
-                agent_load(reinterpret_cast<const uint32_t *>(words + g) + x);
+    // the rows across the cut that a colour reads, from global memory
+    auto refresh = [&](int cy) {
+        for (int c = tid; c < R * pitch32; c += block) {
+            const int q = (int)by_pitch.div((uint32_t)c), x = c - q * pitch32;
+            const size_t g = (size_t)wrap_once(y0 + (cy ? N1 + q : q - R), L1) * L0;
+            reinterpret_cast<uint32_t *>(lab + (N1 + q) * L0)[x] = agent_load(reinterpret_cast<const uint32_t *>(words + g) + x);
         }
     };
     // Meeting of a lattice's parts: every wave's stores and atomics complete,
@@ -314,15 +292,15 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     // and, of the first Philox round, the product of the area's number.
     const uint32_t sd = D == 2 ? (uint32_t)(s * s) : (uint32_t)(s * s * s);
     const uint32_t by_s = 65536u / (uint32_t)s + 1u;  // floor(o / s) = o by_s >> 16 for o < s^D, s <= 15
-    const FastDiv by_na0((uint32_t)na0), by_n1((uint32_t)pt.n1), by_2s(2u * (uint32_t)s), by_s32((uint32_t)s);
+    const FastDiv by_na0((uint32_t)na0), by_n1((uint32_t)n1), by_2s(2u * (uint32_t)s), by_s32((uint32_t)s);
     struct Area {
         uint32_t xy, z, c2, c3;  // corner in the box: x | y << 16, z
     };
     auto area_of = [&](int i) {
         Area r{0, 0, 0, 0};
         const int q0 = (int)by_na0.div((uint32_t)i), ax = i - q0 * na0;
-        const int az = D == 3 ? (int)by_n1.div((uint32_t)q0) : 0, ay = q0 - az * pt.n1;
-        const uint32_t id = (uint32_t)ax + (uint32_t)na0 * ((uint32_t)(pt.a1 + ay) + (uint32_t)na1 * (uint32_t)(pt.a2 + az));
+        const int az = D == 3 ? (int)by_n1.div((uint32_t)q0) : 0, ay = q0 - az * n1;
+        const uint32_t id = (uint32_t)ax + (uint32_t)na0 * ((uint32_t)((LONE ? 0 : pt.a1) + ay) + (uint32_t)na1 * (uint32_t)az);
         const uint64_t p0 = (uint64_t)0xD2511F53u * id;
         r.xy = (uint32_t)(2 * s * ax) | ((uint32_t)(2 * s * ay) << 16);
         r.z = (uint32_t)(2 * s * az);
@@ -386,7 +364,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     uint32_t my_nontrivial = 0, my_accepted = 0;
     int4 *list_spill[2];
     {
-        const size_t off = ((size_t)na0 * na1 * pt.a2 + (size_t)na0 * pt.a1 * pt.n2) * (size_t)a.k;
+        const size_t off = LONE ? 0 : (size_t)na0 * pt.a1 * (size_t)a.k;
         list_spill[0] = plain(a.dlist[0]) + off;
         list_spill[1] = plain(a.dlist[1]) + off;
     }
@@ -543,7 +521,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
         if (!K1) {
             // own accepted copies earlier in this activation
             const int ax = (int)by_2s.div((uint32_t)x), ay = (int)by_2s.div((uint32_t)y), az = D == 3 ? (int)by_2s.div((uint32_t)z) : 0;
-            area = ax + na0 * (ay + pt.n1 * az);
+            area = ax + na0 * (ay + n1 * az);
             for (int i = first_of_area ? 0xFFFF : head[area], next; i != 0xFFFF; i = next) {
                 const int4 r = record(li, p, i, next);
                 if (r.x == lt) { ct.x -= 1; ct.y += r.z; }
@@ -564,7 +542,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
             for (int d = 0; d < D; ++d) u[d] = sh.unit[o][d];
             if (a.pdir) pd = plain(a.pdir)[ls];
             if (a.chem) {
-                const int gx = wrap_once(x + sdx, L0), gy = wrap_once(y0 + y + sdy, L1), gz = D == 3 ? wrap_once(z0 + z + sdz, L2) : 0;
+                const int gx = wrap_once(x + sdx, L0), gy = wrap_once(y0 + y + sdy, L1), gz = D == 3 ? wrap_once(z + sdz, L2) : 0;
                 const int16_t *f = plain(a.chem) + D * (((size_t)gz * L1 + gy) * L0 + gx);
 #pragma unroll
                 for (int d = 0; d < D; ++d) c[d] = f[d];
@@ -646,7 +624,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
         if (HOT && marking) mark(x, y);
         if (EXT && a.csum) move_centroids<D>(a, (int)(site(y, z) + (size_t)x), lt, ls);
         const int4 rec = make_int4(lt, ls, dso, dsn);
-        if (!lone && ((cut1 && (y < R || y >= N1 - R)) || (cut2 && (z < R || z >= N2 - R)))) agent_store(words + site(y, z) + x, nw);
+        if (!lone && (y < R || y >= N1 - R)) agent_store(words + site(y, 0) + x, nw);
         add_copy(pairs_of(p ^ 1), rec);
         if (K1 && last_copy.x < 0) {
             last_copy = rec;
@@ -744,7 +722,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
             marking = sh.hot_n[0] <= hot_cap || sh.hot_n[1] <= hot_cap || sh.hot_n[2] <= hot_cap || sh.hot_n[3] <= hot_cap;
         }
         for (uint32_t alpha = 0; alpha < rl.n_act; ++alpha, parity ^= 1, last_li = li, li = li == 2 ? 0 : li + 1) {
-            if (!lone) refresh((int)((alpha >> 1) & 1), (int)((alpha >> 2) & 1));
+            if (!lone) refresh((int)((alpha >> 1) & 1));
             readd(last_li, parity ^ 1);
             if (!lone) __syncthreads();
             if (tid == 0) sh.list_n[li == 2 ? 0 : li + 1] = 0;
@@ -881,7 +859,7 @@ __device__ __forceinline__ void sweep_resident(const A &a, const ResidentPart &p
     {
         const int per = vec ? L0 / 4 : L0;
         const FastDiv by_per((uint32_t)per);
-        for (int c = tid; c < per * N1 * N2; c += block) {
+        for (int c = tid; c < per * N1 * P2; c += block) {
             int ry, rz;
             const int r = (int)by_per.div((uint32_t)c), x = c - r * per;
             own_row(r, ry, rz);
@@ -984,10 +962,16 @@ __global__ void __launch_bounds__(kResidentMaxThreads) batch_resident_kernel(con
     using ConstArgs = const SweepArgsG __attribute__((address_space(4)));
     using ConstPart = const ResidentPart __attribute__((address_space(4)));
     const ConstPart &cp = ((ConstPart *)parts)[ticket];
-    const ResidentPart pt{cp.lattice, cp.n_parts, cp.a1, cp.n1, cp.a2, cp.n2, cp.n_labels, cp.hot_cap};
+    const ResidentPart pt{cp.lattice, cp.n_parts, cp.a1, cp.n1, cp.n_labels, cp.hot_cap};
     ConstArgs &a = ((ConstArgs *)args)[pt.lattice];
-    if (pt.n_parts == 1) sweep_resident<Cell, D, ACT, SINGLE, K1, EXT, true>(a, pt, rl);
-    else sweep_resident<Cell, D, ACT, SINGLE, K1, EXT, false>(a, pt, rl);
+    // lattices in parts: see resident_pays
+    if constexpr (D == 2 && !(K1 && std::is_same<Cell, char32_t>::value)) {
+        if (pt.n_parts > 1) {
+            sweep_resident<Cell, D, ACT, SINGLE, K1, EXT, false>(a, pt, rl);
+            return;
+        }
+    }
+    sweep_resident<Cell, D, ACT, SINGLE, K1, EXT, true>(a, pt, rl);
 }
 
 // One activation after another of a lattice whose parts did not come
@@ -995,7 +979,7 @@ __global__ void __launch_bounds__(kResidentMaxThreads) batch_resident_kernel(con
 // global memory.  It runs only where the GPU is crowded, and is written to be
 // short: an accepted copy is a record of its area, added to the counters
 // after the activation.
-template <int D, bool ACT>
+template <bool ACT>
 __global__ void __launch_bounds__(kBlock) alone_kernel(const SweepArgs *args, const int64_t *label_off, ResidentLaunch rl)
 {
     __shared__ int32_t j_lds[kMaxTypes * kMaxTypes];
@@ -1014,11 +998,9 @@ __global__ void __launch_bounds__(kBlock) alone_kernel(const SweepArgs *args, co
     static_assert(kMaxTypes * kMaxTypes == kBlock, "one entry of J per thread");
     const SharedTables tables{j_lds, m->LG, reinterpret_cast<const TypeParams *>(m->lam_v)};
     const ThrTables tb{m->TM32, m->TL32, m->TI32, m->n_ti};
-    constexpr int NNB = D == 2 ? 8 : 26;
-    const int L0 = a.L[0], L1 = a.L[1], L2 = a.L[2], s = a.s;
-    const LdsMap<kDirect> map{L0, L1, L0, L1, L2};
-    const int areas = a.na[0] * a.na[1] * a.na[2];
-    const uint32_t sd = (uint32_t)(D == 2 ? s * s : s * s * s);
+    const int L0 = a.L[0], L1 = a.L[1], s = a.s, areas = a.na[0] * a.na[1];
+    const LdsMap<kDirect> map{L0, L1, L0, L1, 1};
+    const uint32_t sd = (uint32_t)(s * s);
     int32_t *cnt = a.counters[0];  // both buffers hold the exact state
     int4 *records = a.dlist[0];    // k per area
     int32_t *n_records = reinterpret_cast<int32_t *>(a.dlist[1]);
@@ -1032,26 +1014,25 @@ __global__ void __launch_bounds__(kBlock) alone_kernel(const SweepArgs *args, co
     for (int i_mcs = 0; i_mcs < rl.n_mcs; ++i_mcs) {
         const uint32_t mcs = rl.mcs0 + (uint32_t)i_mcs;
         for (uint32_t alpha = 0; alpha < rl.n_act; ++alpha) {
-            const int cx = (int)(alpha & 1), cy = (int)((alpha >> 1) & 1), cz = D == 3 ? (int)((alpha >> 2) & 1) : 0;
+            const int cx = (int)(alpha & 1), cy = (int)((alpha >> 1) & 1);
             for (int i = tid; i < areas; i += kBlock) {
-                const int ax = i % a.na[0], ay = i / a.na[0] % a.na[1], az = i / a.na[0] / a.na[1];
+                const int ax = i % a.na[0], ay = i / a.na[0];
                 int4 *own = records + (size_t)i * a.k;
                 int n_own = 0;
                 for (int j = 0; j < a.k; ++j) {
                     const uint4 u = philox4x32_10(make_uint4((uint32_t)i, mcs, (alpha << 8) | (uint32_t)j, a.lattice_id), a.key0, a.key1);
                     const int o = (int)__umulhi(u.x, sd);
-                    const int tx = s * (2 * ax + cx) + o % s, ty = s * (2 * ay + cy) + o / s % s;
-                    const int tz = D == 3 ? s * (2 * az + cz) + o / s / s : 0;
-                    const int nsel = (int)__umulhi(u.y, (uint32_t)NNB);
-                    const int sx = tx + nb_dx<D>(nsel), sy = ty + nb_dy<D>(nsel), sz = tz + nb_dz<D>(nsel);
-                    const int t = map.at(tx, ty, tz), src = map.at(sx, sy, sz);
+                    const int tx = s * (2 * ax + cx) + o % s, ty = s * (2 * ay + cy) + o / s;
+                    const int nsel = (int)(u.y >> 29);
+                    const int sx = tx + nb_dx<2>(nsel), sy = ty + nb_dy<2>(nsel);
+                    const int t = map.at(tx, ty, 0), src = map.at(sx, sy, 0);
                     const int lt = a.lat[t], ls = a.lat[src];
                     if (lt == ls || lt < 0 || ls < 0) continue;
                     ++nontrivial;
                     const int tt = lt == 0 ? 0 : a.cell_type[lt], ts = ls == 0 ? 0 : a.cell_type[ls];
                     int64_t dso, dsn;
-                    if (!evaluate<int32_t, D, ACT, false, kDirect, true>(
-                            a, tb, JRows{}, tables, a.lat, a.act, map, tx, ty, tz, sx, sy, sz, src, lt, ls, tt, ts,
+                    if (!evaluate<int32_t, 2, ACT, false, kDirect, true>(
+                            a, tb, JRows{}, tables, a.lat, a.act, map, tx, ty, 0, sx, sy, 0, src, lt, ls, tt, ts,
                             seen_counters(cnt, lt, own, n_own, own + kOwnInRegs),
                             seen_counters(cnt, ls, own, n_own, own + kOwnInRegs), u.z, dso, dsn))
                         continue;
@@ -1068,7 +1049,7 @@ __global__ void __launch_bounds__(kBlock) alone_kernel(const SweepArgs *args, co
             barrier();
         }
         if (ACT) {
-            for (int i = tid; i < L0 * L1 * L2; i += kBlock) a.act[i] = (uint8_t)max((int)a.act[i] - 1, 0);
+            for (int i = tid; i < L0 * L1; i += kBlock) a.act[i] = (uint8_t)max((int)a.act[i] - 1, 0);
             barrier();
         }
     }
@@ -1139,16 +1120,11 @@ hipError_t launch_resident_act16(const ResidentCall &c, hipStream_t st)
                 : launch_one<char16_t, 3, true, true, false, false>(c, st);
 }
 #elif CPM_RESIDENT_PART == 5
-hipError_t launch_resident_alone(const SweepArgs *args, const int64_t *label_off, int n_lattices, int ndim, bool act,
+hipError_t launch_resident_alone(const SweepArgs *args, const int64_t *label_off, int n_lattices, bool act,
                                  const ResidentLaunch &rl, hipStream_t st)
 {
-    if (ndim == 2) {
-        if (act) alone_kernel<2, true><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
-        else alone_kernel<2, false><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
-    } else {
-        if (act) alone_kernel<3, true><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
-        else alone_kernel<3, false><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
-    }
+    if (act) alone_kernel<true><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
+    else alone_kernel<false><<<n_lattices, kBlock, 0, st>>>(args, label_off, rl);
     return hipGetLastError();
 }
 #endif
