@@ -94,10 +94,13 @@ __device__ __forceinline__ void write_moments(const double *r, double *o)
     auto moments = [](double n, double s1, double s2, double *mv) {
         if (n > 0) {
             // variance (n s2 - s1^2) / n^2, both products with their rounding
-            // errors: s2 / n - mean^2 lost the digits that cancel
+            // errors: s2 / n - mean^2 lost the digits that cancel.  What is
+            // left is the rounding of the sums (of a single value, that of
+            // its square): the variance of one value is 0, and none is negative
             const double p = s1 * s1, pe = fma(s1, s1, -p), q = n * s2, qe = fma(n, s2, -q);
+            const double var = ((q - p) + (qe - pe)) / (n * n);
             mv[0] = s1 / n;
-            mv[1] = ((q - p) + (qe - pe)) / (n * n);
+            mv[1] = n > 1.0 && !(var < 0.0) ? var : 0.0;
         } else {
             mv[0] = 0.0;
             mv[1] = 0.0;

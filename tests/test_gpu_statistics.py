@@ -66,3 +66,67 @@ def test_statistics_match_reference(ndim, K, n_cells):
             np.testing.assert_allclose(ac[i, :, 0].cpu().numpy(), s, rtol=1e-9, atol=1e-9)
             np.testing.assert_array_equal(ac[i, :, 1].cpu().numpy(), n)
     b.close()
+
+
+def _autocorrelation(V, pos, dims):
+    """ref_summary.autocorrelation of long series, by np.correlate."""
+    d = np.diff(pos[:, 1:], axis=0)
+    L = np.asarray(dims, dtype=np.float64)[:pos.shape[2]]
+    d -= L * np.rint(d / L)
+    norm = np.sqrt((d * d).sum(-1))
+    ok = (V[:-1, 1:] > 0) & (V[1:, 1:] > 0) & (norm > 0)
+    u = np.where(ok[..., None], d / np.where(ok, norm, 1.0)[..., None], 0.0)
+    m = len(d)
+    lags = lambda x: np.correlate(x, x, "full")[m - 1:]
+    cells = range(d.shape[1])
+    return (sum(lags(u[:, c, e]) for c in cells for e in range(d.shape[2])),
+            np.rint(sum(lags(ok[:, c].astype(np.float64)) for c in cells)))
+
+
+@pytest.mark.parametrize("ndim,K,n_cells,autocorrelation", [
+    (2, 5200, (2, 1), False),  # one cell's steps no longer fit the LDS: the general kernels
+    (3, 4100, (1,), False),
+    (3, 3610, (1,), True),     # (met by one thread per cell: some seconds)
+])
+def test_series_beyond_the_step_buffer(ndim, K, n_cells, autocorrelation):
+    import torch
+    print(f"{ndim}D, {K} samples", flush=True)
+    rng = np.random.default_rng(K + ndim)
+    b, dims = _batch(ndim, n_cells)
+    recs = [_samples(rng, K, c, ndim, dims[0]) for c in n_cells]
+    for r in recs:  # no drift: the search for the persistence time ends early (one thread per cell)
+        r[..., 2:2 + ndim] = rng.random(r[..., 2:2 + ndim].shape) * dims[0]
+    buf = torch.as_tensor(np.concatenate([r.reshape(-1) for r in recs])).cuda()
+    out = b.summary(buf, K, 3.0).cpu().numpy()
+    for i, r in enumerate(recs):
+        ref = ref_summary.summary(r[..., 0], r[..., 1], r[..., 2:2 + ndim], dims, 3.0)
+        # sums of at most 1e4 terms of size 1: 1e4 * 2^-53, as above
+        np.testing.assert_allclose(out[i], ref, rtol=1e-9, atol=1e-9)
+    ac = b.autocorrelation(buf, K).cpu().numpy() if autocorrelation else None
+    for i, r in enumerate(recs if autocorrelation else []):
+        s, n = _autocorrelation(r[..., 0], r[..., 2:2 + ndim], dims)
+        np.testing.assert_allclose(ac[i, :, 0], s, rtol=1e-9, atol=1e-9)
+        np.testing.assert_array_equal(ac[i, :, 1], n)
+    b.close()
+
+
+def test_variances_of_one_value_and_of_like_values():
+    # one cell: its persistence time has no variance, whatever the rounding of
+    # its square; cells that move alike: no variance falls below zero
+    import torch
+    K, cells = 41, (1, 1, 1, 1, 3, 64, 70)
+    b, dims = _batch(2, cells)
+    rng = np.random.default_rng(9)
+    recs = []
+    for i, c in enumerate(cells):
+        rec = np.repeat(_samples(rng, K, 1, 2, dims[0])[:, 1:], c + 1, axis=1)
+        rec[rec[..., 0] == 0] = rec[0, 0]
+        recs.append(rec)
+    buf = torch.as_tensor(np.concatenate([r.reshape(-1) for r in recs])).cuda()
+    out = b.summary(buf, K, 1.0 / 3.0).cpu().numpy()
+    assert (out[:4, 7] == 0.0).all()
+    assert (out[:, [1, 3, 5, 7]] >= 0.0).all()
+    for i, r in enumerate(recs):
+        ref = ref_summary.summary(r[..., 0], r[..., 1], r[..., 2:4], dims, 1.0 / 3.0)
+        np.testing.assert_allclose(out[i], ref, rtol=1e-9, atol=1e-9)
+    b.close()
