@@ -165,3 +165,18 @@ def test_unaligned_lattice(torch_cuda, layout, act):
         cpm.cpm_destroy(h)
     for x, y in zip(*out):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("n", [16, 64, 65])
+def test_occupancy_rows(torch_cuda, n):
+    # one row of workgroups (which overwrites the counts), the most it takes,
+    # and one lattice more
+    dims = (20, 34)
+    print(f"occupancy of {n} lattices of {dims}", flush=True)
+    lats = [inputs.random_labels((20, 34, 1), 3, 170 + i, p_obstacle=0.2).reshape(1, 34, 20) for i in range(n)]
+    p = cpm.Params(ndim=2, dims=dims, J=np.zeros((3, 3)), lambda_volume=[0, 1, 0], volume_target=[0, 10, 0], obstacle_type=2, sub=1)
+    b = cpm.Batch([p] * n, lats, [np.array([0, 1, 1, 1], dtype=np.int32)] * n)
+    out = torch_cuda.full((20 * 34,), -7, dtype=torch_cuda.int32, device="cuda")
+    for _ in range(2):  # the counts are overwritten
+        cpm.cpm_batch_occupancy(b.handle, out, b.stream)
+        np.testing.assert_array_equal(out.cpu().numpy(), sum((l > 0).astype(np.int64) for l in lats).reshape(-1))
