@@ -1059,12 +1059,14 @@ __global__ void __launch_bounds__(kBlock) alone_kernel(const SweepArgs *args, co
     atomicAdd(reinterpret_cast<unsigned long long *>(a.stats) + 1, (unsigned long long)accepted);
 }
 
+// The attribute belongs to the kernel, which other threads may launch with
+// other sizes: always the same value.
 template <typename F>
 hipError_t allow_lds(F *kernel, size_t lds)
 {
     return lds <= 65536 ? hipSuccess
                         : hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 }
 
 template <typename Cell, int D, bool ACT, bool SINGLE, bool K1, bool EXT>

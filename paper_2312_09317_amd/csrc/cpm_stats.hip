@@ -539,9 +539,9 @@ hipError_t launch_staged(const StatsTables &t, const double *samples, int n_samp
 {
     const int m = n_samples - 1;
     const int splits = stat_splits(t.max_labels, lc, AUTO ? 2 * m : kSums);
-    if (lds > 65536) {
+    if (lds > 65536) {  // (always the same value: other threads may launch with other sizes)
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&staged_stats_kernel<D, AUTO>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStatLds);
         if (e != hipSuccess) return e;
     }
     staged_stats_kernel<D, AUTO><<<(unsigned)t.n * (unsigned)splits, kStatThreads, lds, stream>>>(

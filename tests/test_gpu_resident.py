@@ -348,3 +348,39 @@ def test_many_attempts_per_area_uncut(torch_cuda):
     params, lats, cts = _batch_of(torch_cuda, spec)
     params = [p.replace(temperature=40.0) for p in params]
     _batches_same(torch_cuda, params, lats, cts, "box", 4)
+
+
+def test_lattices_of_two_sizes_swept_by_two_threads(torch_cuda):
+    # one kernel launched with different amounts of LDS from two threads, each
+    # on a stream of its own
+    import threading
+    torch = torch_cuda
+    dims = ((176, 176), (208, 208))
+    sims, streams, want, errors = [], [], [], []
+    for d in dims:
+        lat, n = _lattice("blobs", d, 30, 90, False)
+        ct = np.array([0] + [1] * n, dtype=np.int32)
+        ref = cpm.Simulation(_params(d).replace(layout="in_place"), lat, ct)
+        ref.sweep(40)
+        want.append(ref.lattice.clone())
+        sims.append(cpm.Simulation(_params(d), lat, ct))
+        streams.append(torch.cuda.Stream())
+    torch.cuda.synchronize()
+
+    def run(i):
+        try:
+            with torch.cuda.stream(streams[i]):
+                for _ in range(40):
+                    sims[i].sweep(1)
+        except Exception as e:  # reported by the test
+            errors.append(e)
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors
+    for s, w in zip(sims, want):
+        assert torch.equal(s.lattice, w)
