@@ -287,7 +287,7 @@ const char *cpm_last_error(void);
 /*
  * Batches: n independent lattices (replicates or parameter sweeps, paper,
  * Results, "Serial Cellular Potts Models are limited to sub-millimetre scale",
- * Fig. 1B) advanced together, every activation of all of them in one launch.
+ * Fig. 1B) advanced together.
  * Lattice i follows params[i] (its own dims, energies, temperature, seed,
  * lattice_id); all share ndim, sub, attempts and act_enabled.  Each lattice
  * evolves exactly as it would alone under cpm_sweep.
@@ -307,11 +307,11 @@ int cpm_batch_init(const cpm_params *params, int32_t n, const int32_t *n_cells, 
                    const int32_t *d_cell_types, uint8_t *d_act, void *d_workspace, size_t workspace_bytes,
                    void *stream, cpm_batch **out);
 /* Runs n_mcs MCS of every lattice.  By default, where the library chooses the
- * tiling and the lattices fit, in one launch whose workgroups keep a lattice
- * each (or a part of a large one) in LDS; else each MCS is one launch of an
- * executable HIP graph captured at the first call (the activations, the Act
- * decay and the MCS counter update, kernel nodes only), captured on a private
- * stream and launched on `stream`. */
+ * tiling and the lattices fit and sweep faster that way, in one launch whose
+ * workgroups keep a lattice each (or a part of a large 2D one) in LDS; else
+ * each MCS is one launch of an executable HIP graph captured at the first
+ * call (the activations, the Act decay and the MCS counter update, kernel
+ * nodes only), captured on a private stream and launched on `stream`. */
 int cpm_batch_sweep(cpm_batch *b, int32_t n_mcs, void *stream);
 /* enabled = 0: cpm_batch_sweep launches the graph's kernels one by one (mode
  * 1 of cpm_batch_launch_mode), else it replays the graph (mode 0); same
@@ -350,8 +350,8 @@ int cpm_batch_alone_count(cpm_batch *b, uint64_t *count, void *stream);
  * the acceptance draw u2; every attempt sees the lattice, the activity and
  * the per-cell counters as the attempt before it left them; Act decays at
  * the end of each MCS.  Energies as for cpm_batch_sweep (adhesion, volume,
- * surface, Act, chemotaxis).  One wave per lattice: this is the slow
- * reference, not a fast path.  Shares the MCS counter and the attempt
+ * surface, Act, chemotaxis).  One workgroup per lattice, which evaluates
+ * attempts one after another: the reference, not the fast path.  Shares the MCS counter and the attempt
  * statistics with cpm_batch_sweep, and may be mixed with it. */
 int cpm_batch_sweep_serial(cpm_batch *b, int32_t n_mcs, void *stream);
 /* Per site, the number of lattices of the batch that hold a cell (label

@@ -535,7 +535,8 @@ def cpm_batch_destroy(h: int) -> None:
 
 
 class Batch:
-    """Many lattices on the GPU advanced together (one launch per activation).
+    """Many lattices on the GPU advanced together: kept in LDS over a sweep
+    call where they fit, else by one launch per activation (launch_mode).
 
     `lattices` and `cell_types` are lists of arrays; they are packed back to
     back on the device.

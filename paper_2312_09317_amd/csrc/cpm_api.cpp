@@ -94,7 +94,6 @@ struct cpm_batch {
     uint64_t mcs_run = 0;
     size_t max_sites = 0;
     int64_t max_bricks = 0;          // largest centroid-reduction grid of the lattices
-    bool use_graph = true;
     int mode = 3;                    // 0: one graph replay per MCS, 1: kernels one by one, 2: persistent launch,
                                      // 3: resident where the batch allows it, else 0
     cpm::GridBarrier *bar = nullptr; // barrier of the persistent launch
@@ -1813,7 +1812,6 @@ int cpm_batch_launch_mode(cpm_batch *b, int32_t mode)
     if (mode == 2 && !(b->k == 1 && b->layout == 2))
         return fail(CPM_ENOTSUP, "the persistent launch runs batches swept in place (k = 1)");
     b->mode = mode;
-    b->use_graph = mode == 0;
     return CPM_OK;
 }
 
@@ -1838,7 +1836,6 @@ int cpm_batch_alone_count(cpm_batch *b, uint64_t *count, void *stream)
 int cpm_batch_use_graph(cpm_batch *b, int32_t enabled)
 {
     if (!b) return fail(CPM_EINVAL, "batch is NULL");
-    b->use_graph = enabled != 0;
     b->mode = enabled ? 0 : 1;
     return CPM_OK;
 }

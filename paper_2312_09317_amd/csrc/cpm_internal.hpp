@@ -293,7 +293,7 @@ hipError_t launch_contacts(const SweepArgs &a, int ndim, int n_types, int64_t *o
 hipError_t launch_batch_cell_stats(const SweepArgs *d_args, const int64_t *d_label_off, int n_lattices, int ndim,
                                    int64_t max_bricks, size_t total_labels, int32_t *v_out, int32_t *s_out, int32_t *ref,
                                    int64_t *cent, hipStream_t stream);
-// One MCS of the serial CPM on every lattice of a batch (one wave each),
+// One MCS of the serial CPM on every lattice of a batch (one workgroup each),
 // without the Act decay; counters: the exact buffer `parity`.
 hipError_t launch_serial_mcs(const SweepArgs *d_args, int n_lattices, int ndim, bool act, bool mirror, uint32_t mcs,
                              int parity, hipStream_t st);

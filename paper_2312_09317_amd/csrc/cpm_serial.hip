@@ -2,10 +2,10 @@
 // attempts at uniformly drawn targets, each seeing the lattice and the
 // per-cell counters exactly as the attempt before it left them.  It is the
 // reference the parallel scheme is compared with (Fig. 5, Fig. 6E), run for
-// every lattice of a batch at once: one wave per lattice, attempts one after
-// another.
+// every lattice of a batch at once: one workgroup per lattice, attempts
+// evaluated one after another.
 //
-// One workgroup per lattice.  Its waves draw kDraws attempts per lane at once
+// The workgroup's four waves draw kDraws attempts per lane at once
 // (kRound in all) and read both labels of each: most attempts find two like
 // labels (99% and more of those of single-cell and chemotaxis ensembles) and
 // change nothing.  The others are taken in attempt order, wave after wave,
